@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_aniso_stoch(AnisoCall c, int log_g)
 // estimated as in Sec. 4): per sample the jitter and the jittered level of
 // the stochastic mode (key words 0, 1, 2) sample the low-pass filter; the
 // reconstruction filter is evaluated on that level and shaded once.
-template <int F, int SHADE>
+template <int F, int SHADE, int FMT>
 __global__ __launch_bounds__(256) void k_aniso_split(AnisoCall c, int log_g)
 {
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -175,7 +175,8 @@ __global__ __launch_bounds__(256) void k_aniso_split(AnisoCall c, int log_g)
                     tp[1] = SF_TAP_NONE;
                     tp[2] = SF_TAP_NONE;
                 }
-                const float4 r = recon_level<F>(c.tex, wrap_coord(c.tex.wrap, u), wrap_coord(c.tex.wrap, v), l);
+                const float4 r = recon_level<F, FMT>(c.tex, c.g, wrap_coord(c.tex.wrap, u),
+                                                      wrap_coord(c.tex.wrap, v), l);
                 acc = add4(acc, shade<SHADE>(c.g, r));
             }
         }
@@ -541,7 +542,14 @@ static void launch_a2(const AnisoCall &c, hipStream_t s)
         if (c.mode == SPLIT) {
             const int G = lane_group(c.n, c.spp);
             const int64_t threads = c.n * G;
-            k_aniso_split<F, SHADE><<<dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s>>>(c, __builtin_ctz(G));
+            const dim3 grid((uint32_t)((threads + 255) / 256)), block(256);
+            const int log_g = __builtin_ctz(G);
+            if (c.tex.fmt == SF_RGBA8_UNORM)
+                k_aniso_split<F, SHADE, SF_RGBA8_UNORM><<<grid, block, 0, s>>>(c, log_g);
+            else if (c.tex.fmt == SF_RGBA32F)
+                k_aniso_split<F, SHADE, SF_RGBA32F><<<grid, block, 0, s>>>(c, log_g);
+            else
+                k_aniso_split<F, SHADE, SF_DCT8><<<grid, block, 0, s>>>(c, log_g);
             return;
         }
     }

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void k_filter2d_stoch(Filter2DCall c, int log_
 // Sec. 4): per sample the stochastic level of the key's word 3 (the low-pass
 // filter over levels, sampled), then shade(sum_i w_i t_i) of that level (the
 // reconstruction filter, evaluated before shading).
-template <int F, int SHADE>
+template <int F, int SHADE, int FMT>
 __global__ __launch_bounds__(256) void k_filter2d_split(Filter2DCall c, int log_g)
 {
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void k_filter2d_split(Filter2DCall c, int log_
                     tp[1] = SF_TAP_NONE;
                     tp[2] = SF_TAP_NONE;
                 }
-                acc = add4(acc, shade<SHADE>(c.g, recon_level<F>(c.tex, uu, vv, l)));
+                acc = add4(acc, shade<SHADE>(c.g, recon_level<F, FMT>(c.tex, c.g, uu, vv, l)));
             }
         }
     }
@@ -240,9 +240,21 @@ __global__ __launch_bounds__(256) void k_filter2d_split(Filter2DCall c, int log_
     }
 }
 
-template <int F, int SHADE, int MODE>
+// Every tap on the level pair of lambda.  A lookup of 2 x 16 RGBA8 taps reads
+// eight rows and spends about ten vector instructions per tap (conversions,
+// a table read, four multiply-adds); 2,073,600 of them, GGX-shaded on a
+// 4096^2 pyramid, take 25.8 us, near the 27 us that reading the texture and
+// the queries once takes (filter-before 27.2, GGX-shaded RGBA32F texels of a
+// 1024^2 pyramid 73.7).  With each tap wrapped, loaded and shaded by itself
+// (3,400 instructions per lookup) they took 120, 100 and 101 us.
+template <int F, int SHADE, int MODE, int FMT>
 __global__ __launch_bounds__(256) void k_filter2d_det(Filter2DCall c)
 {
+    constexpr int KIND = tap_kind<SHADE, MODE>();
+    constexpr bool TABLE = KIND == TAP_GGX && FMT == SF_RGBA8_UNORM;
+    __shared__ float spec[TABLE ? 256 : 1];
+    if constexpr (TABLE)
+        build_spec_table(c.g, spec);
     const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (q >= c.n)
         return;
@@ -256,41 +268,16 @@ __global__ __launch_bounds__(256) void k_filter2d_det(Filter2DCall c)
     int l0, l1;
     float f;
     levels_of(c.tex, qq.z, l0, l1, f);
-    constexpr int NT = Taps<F>::n;
-    constexpr int F0 = Taps<F>::first;
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
     for (int li = 0; li < 2; ++li) {
         const float pl = li == 0 ? 1.0f - f : f;
         if (pl == 0.0f)
             continue;
-        const int l = li == 0 ? l0 : l1;
-        int wl = max(1, c.tex.w >> l), hl = max(1, c.tex.h >> l);
-        int ix, iy;
-        float tx, ty, wx[4], wy[4];
-        raster(uu, wl, ix, tx);
-        raster(vv, hl, iy, ty);
-        if constexpr (F == NEAREST) {
-            ix += tx >= 0.5f;
-            iy += ty >= 0.5f;
-        }
-        axis_weights<F>(tx, wx);
-        axis_weights<F>(ty, wy);
-#pragma unroll
-        for (int b = 0; b < NT; ++b) {
-            const int y = wrap_tap(c.tex.wrap, iy + F0 + b, hl);
-#pragma unroll
-            for (int a = 0; a < NT; ++a) {
-                const float wgt = pl * wx[a] * wy[b];
-                float4 t = texel(c.tex, l, wrap_tap(c.tex.wrap, ix + F0 + a, wl), y);
-                float4 v = MODE == BEFORE ? t : shade<SHADE>(c.g, t);
-                sum.x = __builtin_fmaf(wgt, v.x, sum.x);
-                sum.y = __builtin_fmaf(wgt, v.y, sum.y);
-                sum.z = __builtin_fmaf(wgt, v.z, sum.z);
-                sum.w = __builtin_fmaf(wgt, v.w, sum.w);
-            }
-        }
+        const float4 s = level_sum<F, SHADE, KIND, FMT>(c.tex, c.g, spec, uu, vv, li == 0 ? l0 : l1);
+        tap_add(pl, s.x, s.y, s.z, s.w, sum);
     }
-    store<SHADE>(c.out, q, MODE == BEFORE ? shade<SHADE>(c.g, sum) : sum);
+    store<SHADE>(c.out, q, sum_value<SHADE, MODE, FMT>(c.g, sum));
 }
 
 // Deterministic Gaussian comparators, binary32 weights and compensated sums
@@ -393,6 +380,16 @@ static int64_t resident_blocks_smem(K kernel, int smem)
     return std::max<int64_t>(1, (int64_t)std::max(per_cu, 1) * std::max(ncu, 1));
 }
 
+// (unshaded, filtering before and after shading are the same sum)
+template <int F, int SHADE, int FMT>
+static void launch_det(const Filter2DCall &c, dim3 grid, hipStream_t s)
+{
+    if (c.mode == BEFORE || SHADE == SF_SHADE_NONE)
+        k_filter2d_det<F, SHADE, BEFORE, FMT><<<grid, dim3(256), 0, s>>>(c);
+    else if constexpr (SHADE != SF_SHADE_NONE)
+        k_filter2d_det<F, SHADE, AFTER, FMT><<<grid, dim3(256), 0, s>>>(c);
+}
+
 template <int F, int SHADE>
 static void launch_f2(const Filter2DCall &c, hipStream_t s)
 {
@@ -400,8 +397,14 @@ static void launch_f2(const Filter2DCall &c, hipStream_t s)
         if (c.mode == SPLIT) {
             const int G = lane_group(c.n, c.spp);
             const int64_t threads = c.n * G;
-            k_filter2d_split<F, SHADE>
-                <<<dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s>>>(c, __builtin_ctz(G));
+            const dim3 grid((uint32_t)((threads + 255) / 256)), block(256);
+            const int log_g = __builtin_ctz(G);
+            if (c.tex.fmt == SF_RGBA8_UNORM)
+                k_filter2d_split<F, SHADE, SF_RGBA8_UNORM><<<grid, block, 0, s>>>(c, log_g);
+            else if (c.tex.fmt == SF_RGBA32F)
+                k_filter2d_split<F, SHADE, SF_RGBA32F><<<grid, block, 0, s>>>(c, log_g);
+            else
+                k_filter2d_split<F, SHADE, SF_DCT8><<<grid, block, 0, s>>>(c, log_g);
             return;
         }
     }
@@ -444,10 +447,12 @@ static void launch_f2(const Filter2DCall &c, hipStream_t s)
         } else {
             // the B-spline FIS realises the cubic B-spline itself
             constexpr int FD = F == BSPLINE3_FIS ? BSPLINE3 : F;
-            if (c.mode == BEFORE)
-                k_filter2d_det<FD, SHADE, BEFORE><<<grid, block, 0, s>>>(c);
+            if (c.tex.fmt == SF_RGBA8_UNORM)
+                launch_det<FD, SHADE, SF_RGBA8_UNORM>(c, grid, s);
+            else if (c.tex.fmt == SF_RGBA32F)
+                launch_det<FD, SHADE, SF_RGBA32F>(c, grid, s);
             else
-                k_filter2d_det<FD, SHADE, AFTER><<<grid, block, 0, s>>>(c);
+                launch_det<FD, SHADE, SF_DCT8>(c, grid, s);
         }
     }
 }

@@ -561,9 +561,9 @@ __device__ __forceinline__ int ray_setup_dev(const float *wmin, const float *sca
 // D G1(no) G1(ni) F / (4 no ni) is a^2 (F/pi) / ((no + s_o)(ni + s_i) d^2):
 // one reciprocal.  Shaded values decide nothing, so the hardware reciprocal
 // and square root (about 1 ulp each) serve; the result is within a few ulp.
-__device__ __forceinline__ float3 shade_ggx_dev(const GgxConst &g, float4 c)
+__device__ __forceinline__ float ggx_spec(const GgxConst &g, float A)
 {
-    const float r = __builtin_fmaf(g.r_scale, c.w, g.r_bias);
+    const float r = __builtin_fmaf(g.r_scale, A, g.r_bias);
     const float a = r * r;
     const float a2 = a * a;
     const float d = __builtin_fmaf(g.nh2, a2 - 1.0f, 1.0f);
@@ -571,9 +571,19 @@ __device__ __forceinline__ float3 shade_ggx_dev(const GgxConst &g, float4 c)
     const float so = __builtin_amdgcn_sqrtf(__builtin_fmaf(om, g.no2, a2));
     const float si = __builtin_amdgcn_sqrtf(__builtin_fmaf(om, g.ni2, a2));
     const float den = ((g.no + so) * (g.ni + si)) * (d * d);
-    const float spec = (a2 * g.spec_c) * __builtin_amdgcn_rcpf(den);
-    return make_float3(__builtin_fmaf(g.kd[0], c.x, g.ks[0] * spec), __builtin_fmaf(g.kd[1], c.y, g.ks[1] * spec),
-                       __builtin_fmaf(g.kd[2], c.z, g.ks[2] * spec));
+    return (a2 * g.spec_c) * __builtin_amdgcn_rcpf(den);
+}
+
+// Radiance from the albedo and the specular term: linear in both.
+__device__ __forceinline__ float3 ggx_radiance(const GgxConst &g, float x, float y, float z, float spec)
+{
+    return make_float3(__builtin_fmaf(g.kd[0], x, g.ks[0] * spec), __builtin_fmaf(g.kd[1], y, g.ks[1] * spec),
+                       __builtin_fmaf(g.kd[2], z, g.ks[2] * spec));
+}
+
+__device__ __forceinline__ float3 shade_ggx_dev(const GgxConst &g, float4 c)
+{
+    return ggx_radiance(g, c.x, c.y, c.z, ggx_spec(g, c.w));
 }
 
 // a b - c d within about 1.5 ulp (Kahan's algorithm: the rounding error of

@@ -98,14 +98,11 @@ __device__ __forceinline__ float dct_channel(uint32_t wd, float R, float c1x, fl
     return __builtin_fminf(__builtin_fmaxf(v, 0.0f), 1.0f);
 }
 
-// Texel (x, y) of level l, the texture's levels read from `base` (its own
-// base pointer, or a copy of its bytes at the same offsets).
-__device__ __forceinline__ float4 texel(const Tex2DArgs &tx, const uint8_t *base, int l, int x, int y)
+// Texel (x, y) of a level wl texels wide that starts at lv.
+template <int FMT>
+__device__ __forceinline__ float4 texel_at(const Tex2DArgs &tx, const uint8_t *lv, int l, int wl, int x, int y)
 {
-    int wl = max(1, tx.w >> l);
-    int64_t idx = (int64_t)y * wl + x;
-    const uint8_t *lv = base + tx.off[l];
-    if (tx.fmt == SF_DCT8) {
+    if constexpr (FMT == SF_DCT8) {
         const int bw = (wl + 7) >> 3;
         const uint4 b = reinterpret_cast<const uint4 *>(lv)[(int64_t)(y >> 3) * bw + (x >> 3)];
         const float4 R = reinterpret_cast<const float4 *>(tx.dct_range)[l];
@@ -113,13 +110,27 @@ __device__ __forceinline__ float4 texel(const Tex2DArgs &tx, const uint8_t *base
         const float c1x = dct_c1(xi), c2x = dct_c2(xi), c1y = dct_c1(yi), c2y = dct_c2(yi);
         return make_float4(dct_channel(b.x, R.x, c1x, c2x, c1y, c2y), dct_channel(b.y, R.y, c1x, c2x, c1y, c2y),
                            dct_channel(b.z, R.z, c1x, c2x, c1y, c2y), dct_channel(b.w, R.w, c1x, c2x, c1y, c2y));
+    } else if constexpr (FMT == SF_RGBA32F) {
+        return reinterpret_cast<const float4 *>(lv)[(int64_t)y * wl + x];
+    } else {
+        const uint32_t px = reinterpret_cast<const uint32_t *>(lv)[(int64_t)y * wl + x];
+        const float k = 1.0f / 255.0f;
+        return make_float4((float)(px & 0xffu) * k, (float)((px >> 8) & 0xffu) * k, (float)((px >> 16) & 0xffu) * k,
+                           (float)(px >> 24) * k);
     }
+}
+
+// Texel (x, y) of level l, the texture's levels read from `base` (its own
+// base pointer, or a copy of its bytes at the same offsets).
+__device__ __forceinline__ float4 texel(const Tex2DArgs &tx, const uint8_t *base, int l, int x, int y)
+{
+    const int wl = max(1, tx.w >> l);
+    const uint8_t *lv = base + tx.off[l];
+    if (tx.fmt == SF_DCT8)
+        return texel_at<SF_DCT8>(tx, lv, l, wl, x, y);
     if (tx.fmt == SF_RGBA32F)
-        return reinterpret_cast<const float4 *>(lv)[idx];
-    uint32_t px = reinterpret_cast<const uint32_t *>(lv)[idx];
-    const float k = 1.0f / 255.0f;
-    return make_float4((float)(px & 0xffu) * k, (float)((px >> 8) & 0xffu) * k, (float)((px >> 16) & 0xffu) * k,
-                       (float)(px >> 24) * k);
+        return texel_at<SF_RGBA32F>(tx, lv, l, wl, x, y);
+    return texel_at<SF_RGBA8_UNORM>(tx, lv, l, wl, x, y);
 }
 
 __device__ __forceinline__ float4 texel(const Tex2DArgs &tx, int l, int x, int y) { return texel(tx, tx.base, l, x, y); }
@@ -158,15 +169,55 @@ __device__ __forceinline__ bool query_ok(const Tex2DArgs &tx, float3 q)
 
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
-// The reconstruction filter alone on level l at the wrapped coordinate
-// (uu, vv): sum_i w_i t_i with binary32 weights, as the deterministic kernels
-// (the split-filtering estimator shades this once per sample).
-template <int F>
-__device__ __forceinline__ float4 recon_level(const Tex2DArgs &tx, float uu, float vv, int l)
+// Weighted sums of taps.  What is summed is linear in the weights, so that
+// as little as possible is done per tap and the rest once per sum:
+//   TAP_TEXEL   the texel's four channels (RGBA8: bytes, see tap_scale);
+//   TAP_GGX     its albedo channels (likewise) and its specular term, the only
+//               part of the GGX + Lambert model that is not linear in the texel;
+//   TAP_SHADED  the texel shaded as a whole (normal maps).
+enum { TAP_TEXEL = 0, TAP_GGX = 1, TAP_SHADED = 2 };
+
+template <int SHADE, int MODE>
+constexpr int tap_kind()
+{
+    return MODE == BEFORE || SHADE == SF_SHADE_NONE ? TAP_TEXEL : (SHADE == SF_SHADE_GGX ? TAP_GGX : TAP_SHADED);
+}
+
+// The specular terms of the 256 roughness bytes, built by a workgroup of 256
+// lanes: for RGBA8 textures a tap's specular term is a table read instead of
+// two square roots and a reciprocal (the same binary32 numbers).
+__device__ __forceinline__ void build_spec_table(const GgxConst &g, float *table)
+{
+    const float k = 1.0f / 255.0f;
+    table[threadIdx.x] = ggx_spec(g, (float)threadIdx.x * k);
+    __syncthreads();
+}
+
+// Texels of one row as one load from a 4-byte aligned address.
+typedef uint32_t rgba8x2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t rgba8x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ void tap_add(float w, float x, float y, float z, float a, float4 &s)
+{
+    s.x = __builtin_fmaf(w, x, s.x);
+    s.y = __builtin_fmaf(w, y, s.y);
+    s.z = __builtin_fmaf(w, z, s.z);
+    s.w = __builtin_fmaf(w, a, s.w);
+}
+
+// sum_i w_i tap_i of the reconstruction filter F on level l at the wrapped
+// coordinate (uu, vv), rows first.  RGBA8 taps that all lie inside the level
+// are read with one load per row, issued before the first is used; others
+// wrap and load one by one.  `spec`: the table of
+// build_spec_table (RGBA8 with TAP_GGX).
+template <int F, int SHADE, int KIND, int FMT>
+__device__ __forceinline__ float4 level_sum(const Tex2DArgs &tx, const GgxConst &g, const float *spec, float uu,
+                                            float vv, int l)
 {
     constexpr int NT = Taps<F>::n;
     constexpr int F0 = Taps<F>::first;
     const int wl = max(1, tx.w >> l), hl = max(1, tx.h >> l);
+    const uint8_t *lv = tx.base + tx.off[l];
     int ix, iy;
     float fx, fy, wx[4], wy[4];
     raster(uu, wl, ix, fx);
@@ -178,20 +229,114 @@ __device__ __forceinline__ float4 recon_level(const Tex2DArgs &tx, float uu, flo
     axis_weights<F>(fx, wx);
     axis_weights<F>(fy, wy);
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (FMT == SF_RGBA8_UNORM) {
+        uint32_t px[NT][NT];
+        const int x0 = ix + F0, y0 = iy + F0;
+        if ((x0 >= 0) & (x0 + NT <= wl) & (y0 >= 0) & (y0 + NT <= hl)) {
+            const uint32_t *row = reinterpret_cast<const uint32_t *>(lv) + ((int64_t)y0 * wl + x0);
 #pragma unroll
-    for (int b = 0; b < NT; ++b) {
-        const int y = wrap_tap(tx.wrap, iy + F0 + b, hl);
+            for (int b = 0; b < NT; ++b, row += wl) {
+                if constexpr (NT == 4) {
+                    const rgba8x4 v = *reinterpret_cast<const rgba8x4 *>(row);
+                    px[b][0] = v.x, px[b][1] = v.y, px[b][2] = v.z, px[b][3] = v.w;
+                } else if constexpr (NT == 2) {
+                    const rgba8x2 v = *reinterpret_cast<const rgba8x2 *>(row);
+                    px[b][0] = v.x, px[b][1] = v.y;
+                } else {
+                    px[b][0] = *row;
+                }
+            }
+        } else {
+            int xs[NT];
 #pragma unroll
-        for (int a = 0; a < NT; ++a) {
-            const float wgt = wx[a] * wy[b];
-            const float4 t = texel(tx, l, wrap_tap(tx.wrap, ix + F0 + a, wl), y);
-            sum.x = __builtin_fmaf(wgt, t.x, sum.x);
-            sum.y = __builtin_fmaf(wgt, t.y, sum.y);
-            sum.z = __builtin_fmaf(wgt, t.z, sum.z);
-            sum.w = __builtin_fmaf(wgt, t.w, sum.w);
+            for (int a = 0; a < NT; ++a)
+                xs[a] = wrap_tap(tx.wrap, x0 + a, wl);
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                const uint32_t *row = reinterpret_cast<const uint32_t *>(lv) +
+                                      (int64_t)wrap_tap(tx.wrap, y0 + b, hl) * wl;
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+                    px[b][a] = row[xs[a]];
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            float4 row = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                const uint32_t p = px[b][a];
+                const float x = (float)(p & 0xffu), y = (float)((p >> 8) & 0xffu), z = (float)((p >> 16) & 0xffu);
+                if constexpr (KIND == TAP_TEXEL) {
+                    tap_add(wx[a], x, y, z, (float)(p >> 24), row);
+                } else if constexpr (KIND == TAP_GGX) {
+                    tap_add(wx[a], x, y, z, spec[p >> 24], row);
+                } else {
+                    const float k = 1.0f / 255.0f;
+                    const float4 v = shade<SHADE>(g, make_float4(x * k, y * k, z * k, (float)(p >> 24) * k));
+                    tap_add(wx[a], v.x, v.y, v.z, v.w, row);
+                }
+            }
+            tap_add(wy[b], row.x, row.y, row.z, row.w, sum);
+        }
+    } else {
+        int xs[NT];
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+            xs[a] = wrap_tap(tx.wrap, ix + F0 + a, wl);
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int y = wrap_tap(tx.wrap, iy + F0 + b, hl);
+            float4 row = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                float4 t = texel_at<FMT>(tx, lv, l, wl, xs[a], y);
+                if constexpr (KIND == TAP_GGX)
+                    t.w = ggx_spec(g, t.w);
+                else if constexpr (KIND == TAP_SHADED)
+                    t = shade<SHADE>(g, t);
+                tap_add(wx[a], t.x, t.y, t.z, t.w, row);
+            }
+            tap_add(wy[b], row.x, row.y, row.z, row.w, sum);
         }
     }
     return sum;
+}
+
+// A sum of taps as texel values (or radiance, once finished by sum_radiance):
+// RGBA8 sums hold bytes.
+template <int KIND, int FMT>
+__device__ __forceinline__ float4 sum_scaled(float4 s)
+{
+    if constexpr (FMT != SF_RGBA8_UNORM || KIND == TAP_SHADED)
+        return s;
+    const float k = 1.0f / 255.0f;
+    return make_float4(s.x * k, s.y * k, s.z * k, KIND == TAP_TEXEL ? s.w * k : s.w);
+}
+
+// The lookup's value from its sum over all taps and levels.
+template <int SHADE, int MODE, int FMT>
+__device__ __forceinline__ float4 sum_value(const GgxConst &g, float4 sum)
+{
+    constexpr int KIND = tap_kind<SHADE, MODE>();
+    const float4 s = sum_scaled<KIND, FMT>(sum);
+    if constexpr (KIND == TAP_GGX) {
+        const float3 v = ggx_radiance(g, s.x, s.y, s.z, s.w);
+        return make_float4(v.x, v.y, v.z, 0.0f);
+    } else if constexpr (KIND == TAP_TEXEL) {
+        return shade<SHADE>(g, s);
+    } else {
+        return s;
+    }
+}
+
+// The reconstruction filter alone on level l at the wrapped coordinate
+// (uu, vv): sum_i w_i t_i with binary32 weights, as the deterministic kernels
+// (the split-filtering estimator shades this once per sample).
+template <int F, int FMT>
+__device__ __forceinline__ float4 recon_level(const Tex2DArgs &tx, const GgxConst &g, float uu, float vv, int l)
+{
+    return sum_scaled<TAP_TEXEL, FMT>(level_sum<F, SF_SHADE_NONE, TAP_TEXEL, FMT>(tx, g, nullptr, uu, vv, l));
 }
 
 }  // namespace sfk

@@ -48,3 +48,44 @@ def test_dct_codes_at_block_and_workgroup_edges(sf, orc, w, h):
         n = 16 * (-(-x.shape[1] // 8)) * (-(-x.shape[0] // 8))
         assert np.array_equal(buf[gt.offsets[l]:gt.offsets[l] + n], ot.buf[ot.off[l]:ot.off[l] + n]), l
     assert np.array_equal(gt.ranges.cpu().numpy(), ot.dct_range)
+
+
+def _filter_case(orc, sf, lv, wrap, mip):
+    fmt = orc.RGBA8 if lv[0].dtype == np.uint8 else orc.RGBA32F
+    from paper_2407_06107_amd import inputs
+    buf, offs = inputs.pack_levels(lv)
+    h, w = lv[0].shape[:2]
+    ot = orc.Tex2D(buf, w, h, len(lv), fmt, offs, getattr(orc, wrap), getattr(orc, "MIP_LINEAR" if mip else "MIP_NONE"))
+    gt = sf.Texture2D(lv, wrap=getattr(sf, "SF_WRAP_" + wrap), mip=sf.SF_MIP_LINEAR if mip else sf.SF_MIP_NONE)
+    return ot, gt
+
+
+# a level as narrow as, one narrower and one wider than the taps of a row;
+# every tap inside, across each border and (1 x 1) all on one texel
+@pytest.mark.parametrize("w, h", [(1, 1), (2, 3), (4, 4), (5, 4), (3, 6), (8, 5), (67, 33)])
+@pytest.mark.parametrize("wrap", ["REPEAT", "CLAMP"])
+@pytest.mark.parametrize("filt", ["NEAREST", "LINEAR", "BSPLINE3", "KEYS3", "MITCHELL"])
+@pytest.mark.parametrize("dtype", [np.uint8, np.float32])
+def test_every_tap_at_texture_borders(sf, orc, w, h, wrap, filt, dtype):
+    """Filter before, exact after and split, shaded and plain, on levels whose
+    rows the taps do and do not fit in.  Tolerance: values 1e-5; where the
+    filter has negative lobes, 1e-5 of 1.6 times the largest value."""
+    _case("every_tap", w, h, wrap, filt, np.dtype(dtype).name)
+    lv = _pyramid(w, h, 7 * w + h)
+    if dtype == np.float32:
+        lv = [x.astype(np.float32) / np.float32(255) for x in lv]
+    ot, gt = _filter_case(orc, sf, lv, wrap, True)
+    rng = np.random.default_rng(w + h)
+    q = np.empty((600, 3), np.float32)
+    q[:, :2] = rng.random((600, 2)) * 1.2 - 0.1
+    q[:, 2] = rng.random(600) * len(lv)
+    q[:8, :2] = [[0, 0], [1, 1], [0, 1], [0.5, 0.5], [1 - 2**-24, 0], [0.5 / w, 0.5 / h], [1 - 0.5 / w, 0.25], [0.25, 1]]
+    qd = torch.from_numpy(q).cuda()
+    f = getattr(orc, filt)
+    for mode, gmode, spp in ((orc.BEFORE, sf.SF_BEFORE, 1), (orc.AFTER, sf.SF_AFTER_EXACT, 1), (orc.SPLIT, sf.SF_SPLIT, 3)):
+        for shade in (0, 1):
+            ref = orc.filter2d(ot, q, f, mode, spp=spp, seed=5, shade=shade)
+            out = sf.sf_filter2d(gt, qd, sf.sampling(getattr(sf, "SF_" + filt), gmode, spp, seed=5), shade,
+                                 sf.ggx()).cpu().numpy()
+            atol = 1e-7 if filt not in ("KEYS3", "MITCHELL") else 1.6e-5 * np.abs(ref).max()
+            assert np.allclose(out, ref, rtol=1e-5, atol=atol), (mode, shade, np.abs(out - ref).max())
