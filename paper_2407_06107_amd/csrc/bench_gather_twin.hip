@@ -19,9 +19,9 @@
 
 namespace sfk {
 
-__global__ __launch_bounds__(256) void k_ray_gather_twin(RaymarchCall c, uint32_t nb_pad)
+__global__ __launch_bounds__(256) void k_ray_gather_twin(RaymarchCall c, uint32_t log_run)
 {
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, nb_pad) * 256 + threadIdx.x;
+    const int64_t i = (int64_t)xcd_block(blockIdx.x, log_run) * 256 + threadIdx.x;
     if (i >= c.n)
         return;
     RayGeom g;
@@ -117,7 +117,7 @@ extern "C" int sfb_gather_twin(const void *grid, int32_t nx, int32_t ny, int32_t
     c.steps = steps;
     c.spp = 1;
     c.T = T;
-    const uint32_t nb = (uint32_t)((n + 255) / 256), nb_pad = (nb + 7u) & ~7u;
-    sfk::k_ray_gather_twin<<<dim3(nb_pad), dim3(256), 0, (hipStream_t)stream>>>(c, nb_pad);
+    const sfk::XcdGrid xg((uint32_t)((n + 255) / 256), 256);
+    sfk::k_ray_gather_twin<<<dim3(xg.blocks), dim3(256), 0, (hipStream_t)stream>>>(c, xg.log_run);
     return (int)hipGetLastError();
 }

@@ -856,13 +856,13 @@ __device__ __forceinline__ float decode_loaded(const MlpFrags<C, 1> &F, const St
 // Three wavefronts per SIMD overlap one wavefront's vector work with
 // another's matrix work.
 template <int F_, int FMT, bool DBG, bool OFF32>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_neural_ray(NeuralCall c, uint32_t nb_pad)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_neural_ray(NeuralCall c, uint32_t log_run)
 {
     constexpr int C = 16;
     constexpr uint32_t kPointBytes = FMT == SF_LATENT_BF16 ? 32u : 16u;
     MlpFrags<C, 1> Fr;
     load_frags<C, 1>(static_cast<const uint16_t *>(c.mlp.params), Fr);
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, nb_pad) * 256 + threadIdx.x;
+    const int64_t i = (int64_t)xcd_block(blockIdx.x, log_run) * 256 + threadIdx.x;
     const bool active = i < c.n;
     RayGeom g = {};
     int st = 1;
@@ -1089,47 +1089,46 @@ static bool addr64_forced()
 }
 
 template <int F_, int FMT>
-static void launch_nr_m(const NeuralCall &c, hipStream_t s, dim3 grid, uint32_t nb_pad)
+static void launch_nr_m(const NeuralCall &c, hipStream_t s, dim3 grid, uint32_t log_run)
 {
     dim3 block(256);
     const uint64_t bytes = (uint64_t)c.lat.res[0] * c.lat.res[1] * c.lat.res[2] * (FMT == SF_LATENT_BF16 ? 32u : 16u);
     const bool off32 = bytes <= (uint64_t)kNoLatent && !addr64_forced();
     if (c.taps) {
         if (off32)
-            k_neural_ray<F_, FMT, true, true><<<grid, block, 0, s>>>(c, nb_pad);
+            k_neural_ray<F_, FMT, true, true><<<grid, block, 0, s>>>(c, log_run);
         else
-            k_neural_ray<F_, FMT, true, false><<<grid, block, 0, s>>>(c, nb_pad);
+            k_neural_ray<F_, FMT, true, false><<<grid, block, 0, s>>>(c, log_run);
     } else {
         if (off32)
-            k_neural_ray<F_, FMT, false, true><<<grid, block, 0, s>>>(c, nb_pad);
+            k_neural_ray<F_, FMT, false, true><<<grid, block, 0, s>>>(c, log_run);
         else
-            k_neural_ray<F_, FMT, false, false><<<grid, block, 0, s>>>(c, nb_pad);
+            k_neural_ray<F_, FMT, false, false><<<grid, block, 0, s>>>(c, log_run);
     }
 }
 
 template <int F_>
-static void launch_nr_f(const NeuralCall &c, hipStream_t s, dim3 grid, uint32_t nb_pad)
+static void launch_nr_f(const NeuralCall &c, hipStream_t s, dim3 grid, uint32_t log_run)
 {
     if (c.lat.fmt == SF_LATENT_BF16)
-        launch_nr_m<F_, SF_LATENT_BF16>(c, s, grid, nb_pad);
+        launch_nr_m<F_, SF_LATENT_BF16>(c, s, grid, log_run);
     else
-        launch_nr_m<F_, SF_LATENT_FP8E4M3>(c, s, grid, nb_pad);
+        launch_nr_m<F_, SF_LATENT_FP8E4M3>(c, s, grid, log_run);
 }
 
 hipError_t launch_neural_ray(const NeuralCall &c, hipStream_t s)
 {
-    const uint32_t nb = (uint32_t)((c.n + 255) / 256);
-    const uint32_t nb_pad = (nb + 7u) & ~7u;
-    dim3 grid(nb_pad);
+    const XcdGrid xg((uint32_t)((c.n + 255) / 256), 256);
+    dim3 grid(xg.blocks);
     switch (c.filter) {
     case NEAREST:
-        launch_nr_f<NEAREST>(c, s, grid, nb_pad);
+        launch_nr_f<NEAREST>(c, s, grid, xg.log_run);
         break;
     case LINEAR:
-        launch_nr_f<LINEAR>(c, s, grid, nb_pad);
+        launch_nr_f<LINEAR>(c, s, grid, xg.log_run);
         break;
     default:
-        launch_nr_f<BSPLINE3>(c, s, grid, nb_pad);
+        launch_nr_f<BSPLINE3>(c, s, grid, xg.log_run);
         break;
     }
     return hipGetLastError();

@@ -506,13 +506,14 @@ struct Taps {
 };
 
 // Workgroups are dispatched round-robin over the 8 XCDs of the chip; map the
-// hardware block index to a logical one so that consecutive logical blocks
-// (neighbouring tiles of the query stream) land on the same XCD and share
-// its L2.  nb_pad must be a multiple of 8; logical indices >= the real block
-// count are idle.
-__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb_pad)
+// hardware block index to a logical one so that runs of 2^log_run consecutive
+// logical blocks (neighbouring tiles of the query stream) land on the same
+// XCD and share its L2, the runs going round the XCDs in turn.  Logical
+// indices >= the real block count are idle (see XcdGrid).
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t log_run)
 {
-    return (b & 7u) * (nb_pad >> 3) + (b >> 3);
+    const uint32_t j = b >> 3;   // the block's place on its XCD
+    return ((((j >> log_run) << 3) | (b & 7u)) << log_run) | (j & ((1u << log_run) - 1u));
 }
 
 // ------------------------------------------------------------ ray geometry

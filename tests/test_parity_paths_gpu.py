@@ -89,3 +89,42 @@ def test_every_tap_at_texture_borders(sf, orc, w, h, wrap, filt, dtype):
                                  sf.ggx()).cpu().numpy()
             atol = 1e-7 if filt not in ("KEYS3", "MITCHELL") else 1.6e-5 * np.abs(ref).max()
             assert np.allclose(out, ref, rtol=1e-5, atol=atol), (mode, shade, np.abs(out - ref).max())
+
+
+# ------------------------------------------------------------------ ray marches
+def _grids(orc, sf, data, side=1.0, brick=None):
+    nz, ny, nx = data.shape
+    scale = (nx / side, ny / side, nz / side)
+    return orc.Grid(data, scale=scale), sf.Volume(torch.from_numpy(data).cuda(), scale=scale, brick_log2=brick)
+
+
+@pytest.fixture(scope="module")
+def cloud48():
+    from paper_2407_06107_amd import inputs
+    return inputs.cloud_grid(48, seed=4).numpy()
+
+
+# a ray's steps are split over up to 16 wavefronts, in segments of at least 8
+@pytest.mark.parametrize("steps", [1, 15, 16, 31, 33, 128, 257])
+@pytest.mark.parametrize("n, spp", [(1, 2), (63, 1), (65, 3), (1030, 1)])
+def test_march_split_into_segments(sf, orc, cloud48, steps, n, spp):
+    """Stochastic and every-tap marches of few rays, misses and a non-finite
+    ray among them, with and without the brick mask (bit-identical)."""
+    from paper_2407_06107_amd import inputs
+    _case("march_split", steps, n, spp)
+    data = np.ascontiguousarray(cloud48[:40, :36, :44])
+    rays = inputs.random_rays(n, 1.0, seed=steps + n)
+    if n > 2:
+        rays[1, 7] = rays[1, 6]
+        rays[2, 3] = np.nan
+    rd = torch.from_numpy(rays).cuda()
+    og, vol = _grids(orc, sf, data)
+    _, volm = _grids(orc, sf, data, brick=2)
+    for filt in ("LINEAR", "BSPLINE3"):
+        for mode, gmode in ((orc.STOCHASTIC, sf.SF_STOCHASTIC), (orc.BEFORE, sf.SF_BEFORE), (orc.AFTER, sf.SF_AFTER_EXACT)):
+            ref = orc.raymarch(og, rays, steps, getattr(orc, filt), mode, spp=spp, seed=3)
+            smp = sf.sampling(getattr(sf, "SF_" + filt), gmode, spp, seed=3)
+            T = sf.sf_raymarch(vol, rd, steps, smp).cpu().numpy()
+            assert np.allclose(T, ref, rtol=1e-5, atol=1e-7, equal_nan=True), (filt, gmode)
+            Tm = sf.sf_raymarch(volm, rd, steps, smp).cpu().numpy()
+            assert np.array_equal(T, Tm, equal_nan=True), (filt, gmode)
