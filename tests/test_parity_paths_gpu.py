@@ -128,3 +128,54 @@ def test_march_split_into_segments(sf, orc, cloud48, steps, n, spp):
             assert np.allclose(T, ref, rtol=1e-5, atol=1e-7, equal_nan=True), (filt, gmode)
             Tm = sf.sf_raymarch(volm, rd, steps, smp).cpu().numpy()
             assert np.array_equal(T, Tm, equal_nan=True), (filt, gmode)
+
+
+# coherent rays take their taps from a box staged in LDS; the sizes have rows
+# shorter than a staged unit, odd rows, and boxes across every face of the grid
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 2, 3), (13, 9, 7), (40, 36, 44), (41, 35, 43)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("scale", [1.0, 40.0, 3000.0])
+def test_every_tap_march_of_coherent_rays(sf, orc, cloud48, shape, dtype, scale):
+    """Before and exact after against the oracle where a step's extinctions
+    lie below, around and far above the bound of the polynomial form (1/16),
+    with negative densities among them; the brick mask changes no bit."""
+    from paper_2407_06107_amd import inputs
+    _case("every_tap_march", shape, np.dtype(dtype).name, scale)
+    nz, ny, nx = shape
+    data = np.ascontiguousarray(cloud48[4:4 + nz, 6:6 + ny, 2:2 + nx].astype(np.float32) * scale / 50).astype(dtype)
+    if scale == 40.0:
+        data[::3, ::2, ::5] *= dtype(-0.01)
+    rays = inputs.ortho_rays(20, 16, side=1.0, seed=nx)
+    # and segments that run past the grid on both sides
+    rays[::7, 6] -= 0.2
+    rays[::5, 7] += 0.3
+    rd = torch.from_numpy(rays).cuda()
+    og, vol = _grids(orc, sf, data)
+    _, volm = _grids(orc, sf, data, brick=1)
+    for filt in ("NEAREST", "LINEAR", "BSPLINE3"):
+        for mode, gmode in ((orc.BEFORE, sf.SF_BEFORE), (orc.AFTER, sf.SF_AFTER_EXACT)):
+            ref = orc.raymarch(og, rays, 40, getattr(orc, filt), mode)
+            T = sf.sf_raymarch(vol, rd, 40, sf.sampling(getattr(sf, "SF_" + filt), gmode)).cpu().numpy()
+            assert np.allclose(T, ref, rtol=1e-5, atol=1e-7), (filt, gmode, np.abs(T - ref).max())
+            Tm = sf.sf_raymarch(volm, rd, 40, sf.sampling(getattr(sf, "SF_" + filt), gmode)).cpu().numpy()
+            assert np.array_equal(T, Tm), (filt, gmode)
+
+
+def test_every_tap_march_of_non_finite_voxels(sf, cloud48):
+    """A NaN or infinite voxel reaches the rays whose taps hold it and no others."""
+    from paper_2407_06107_amd import inputs
+    _case("every_tap_nan")
+    data = np.ascontiguousarray(cloud48[:40, :36, :44])
+    rd = torch.from_numpy(inputs.ortho_rays(20, 16, side=1.0, seed=5)).cuda()
+    clean = sf.Volume(torch.from_numpy(data).cuda(), side=1.0)
+    bad = data.copy()
+    bad[20, 18, 22] = np.nan
+    bad[8, 8, 8] = np.inf
+    vol = sf.Volume(torch.from_numpy(bad).cuda(), side=1.0)
+    for gmode in (sf.SF_BEFORE, sf.SF_AFTER_EXACT):
+        smp = sf.sampling(sf.SF_BSPLINE3, gmode)
+        a, b = (sf.sf_raymarch(v, rd, 64, smp).cpu().numpy() for v in (clean, vol))
+        hit = np.isnan(b)
+        assert hit.any() and not hit.all()
+        same = a == b
+        assert (same | hit | (b < a)).all() and same.mean() > 0.3
