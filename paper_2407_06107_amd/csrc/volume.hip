@@ -8,6 +8,8 @@
 // it forms the raster position, hashes (ray, sample, step, seed), picks one
 // tap per axis by inverse CDF on the separable weights (Sec. 4.1 FRS) and
 // gathers ONE voxel; the optical depth is a compensated binary32 sum.
+#include <type_traits>
+
 #include "volume_dev.hpp"
 
 #pragma clang fp contract(off)
@@ -30,37 +32,51 @@ struct PlanckConst {
     static constexpr double K(double nm) { return h * c / (nm * 1e-9 * k) * 1.4426950408889634074; }
 };
 
-__device__ __forceinline__ float planck_band(float r, float A, float K)
+// e^x - 1 of y = x log2(e) below y = 0.72 (x = 1/2).
+__device__ __forceinline__ float expm1_small(float y)
 {
-    const float y = K * r;   // x log2(e)
-    float em1;
-    if (y < 0.72134752f) {
-        const float x = y * 0.69314718f;
-        float p = __builtin_fmaf(x, 1.0f / 5040.0f, 1.0f / 720.0f);
-        p = __builtin_fmaf(x, p, 1.0f / 120.0f);
-        p = __builtin_fmaf(x, p, 1.0f / 24.0f);
-        p = __builtin_fmaf(x, p, 1.0f / 6.0f);
-        p = __builtin_fmaf(x, p, 0.5f);
-        p = __builtin_fmaf(x, p, 1.0f);
-        em1 = x * p;
-    } else {
-        em1 = __builtin_amdgcn_exp2f(y) - 1.0f;   // +inf beyond y = 128: B = 0
-    }
-    return A * __builtin_amdgcn_rcpf(em1);
+    const float x = y * 0.69314718f;
+    float p = __builtin_fmaf(x, 1.0f / 5040.0f, 1.0f / 720.0f);
+    p = __builtin_fmaf(x, p, 1.0f / 120.0f);
+    p = __builtin_fmaf(x, p, 1.0f / 24.0f);
+    p = __builtin_fmaf(x, p, 1.0f / 6.0f);
+    p = __builtin_fmaf(x, p, 0.5f);
+    p = __builtin_fmaf(x, p, 1.0f);
+    return x * p;
 }
 
+// PLANCK_HOT: at and above it a band may need the polynomial.
+constexpr float PLANCK_HOT = 41000.0f;
+
+// The three bands side by side: with a branch per band (three exponentials
+// one after the other under three execution masks) 1 Mi rays x 256 steps of
+// the 512^3 fire took 774 us stochastic, and take 725.  The polynomial is needed only beyond 41,000 K (or below
+// 0 K): one test for the wavefront, on the band that needs it first (COOL:
+// none, T is known to lie in [0, PLANCK_HOT)).
+template <bool COOL = false>
 __device__ __forceinline__ void planck3(float T, float B[3])
 {
-    constexpr float A0 = (float)PlanckConst::A(700.0), A1 = (float)PlanckConst::A(546.1),
-                    A2 = (float)PlanckConst::A(435.8);
-    constexpr float K0 = (float)PlanckConst::K(700.0), K1 = (float)PlanckConst::K(546.1),
-                    K2 = (float)PlanckConst::K(435.8);
+    constexpr float A[3] = {(float)PlanckConst::A(700.0), (float)PlanckConst::A(546.1), (float)PlanckConst::A(435.8)};
+    constexpr float K[3] = {(float)PlanckConst::K(700.0), (float)PlanckConst::K(546.1), (float)PlanckConst::K(435.8)};
+    constexpr float SMALL = 0.72134752f;
     float r = __builtin_amdgcn_rcpf(T);
     r = __builtin_fmaf(__builtin_fmaf(-T, r, 1.0f), r, r);   // one Newton step
+    float y[3], em1[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        y[k] = K[k] * r;   // x log2(e)
+        em1[k] = __builtin_amdgcn_exp2f(y[k]) - 1.0f;   // +inf beyond y = 128: B = 0
+    }
+    static_assert(K[0] > 1.001f * SMALL * PLANCK_HOT && K[0] < K[1] && K[1] < K[2], "no polynomial below PLANCK_HOT");
+    if (!COOL && __any(y[0] < SMALL)) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            em1[k] = y[k] < SMALL ? expm1_small(y[k]) : em1[k];
+    }
     const bool cold = T <= 0.0f;
-    B[0] = cold ? 0.0f : planck_band(r, A0, K0);
-    B[1] = cold ? 0.0f : planck_band(r, A1, K1);
-    B[2] = cold ? 0.0f : planck_band(r, A2, K2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        B[k] = cold ? 0.0f : A[k] * __builtin_amdgcn_rcpf(em1[k]);
 }
 
 // ---------------------------------------------------------------- ray march
@@ -652,34 +668,22 @@ __device__ __forceinline__ PerpFrame perp_frame(const float *r8, const float *sc
 }
 
 // The samples of a ray are spread over G = 2^log_g adjacent lanes (a
-// power of two up to 64, inside one wave) and their sums reduced by a
-// butterfly, so small images with many samples still fill the chip.
+// power of two up to 64, inside one wave) and its steps over 2^log_split
+// wavefronts; their sums meet in a butterfly and in LDS, so small images
+// still fill the chip.
 template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2, bool JIT = false>
-__global__ __launch_bounds__(256) void k_emit_stoch(RaymarchCall c, uint32_t log_run, int log_g)
+__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCall c, uint32_t log_run,
+                                                                     uint32_t log_split, int log_g)
 {
-    const int64_t gid = (int64_t)xcd_block(blockIdx.x, log_run) * 256 + threadIdx.x;
+    __shared__ float part[MAX_SPLIT_WAVES][64][3];
+    const RaySegment rg(log_run, log_split, c.steps);
     const int G = 1 << log_g;
-    const int64_t i = gid >> log_g;
-    const int lane = (int)(gid & (G - 1));
-    if (i >= c.n)
-        return;   // the whole group of lanes shares i
-    RayGeom g;
-    int st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    if (st != 0) {
-        const float v = st == 1 ? 0.0f : __builtin_nanf("");
-        if (lane == 0) {
-            c.T[3 * i] = v;
-            c.T[3 * i + 1] = v;
-            c.T[3 * i + 2] = v;
-        }
-        if constexpr (DBG) {
-            const int64_t per = (int64_t)3 * c.steps;
-            for (int s = lane; s < c.spp; s += G)
-                for (int64_t k = 0; k < per; ++k)
-                    c.taps[((int64_t)i * c.spp + s) * per + k] = SF_TAP_NONE;
-        }
-        return;
-    }
+    const int64_t i = rg.i >> log_g;
+    const int lane = rg.lane & (G - 1);
+    RayGeom g = {};
+    int st = 3;   // no ray (the whole group of lanes shares i)
+    if (i < c.n)
+        st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     __amdgpu_buffer_rsrc_t rm;
@@ -689,17 +693,18 @@ __global__ __launch_bounds__(256) void k_emit_stoch(RaymarchCall c, uint32_t log
     acc[0].init();
     acc[1].init();
     acc[2].init();
-    PerpFrame pf;
+    PerpFrame pf = {};
     if constexpr (JIT)
-        pf = perp_frame(c.rays + 8 * i, c.vol.scale, c.footprint);
-    for (int s = lane; s < c.spp; s += G) {
+        if (st == 0)
+            pf = perp_frame(c.rays + 8 * i, c.vol.scale, c.footprint);
+    for (int s = st == 0 ? lane : c.spp; s < c.spp; s += G) {
         StepHash h, hj;
         h.init((uint32_t)i, (uint32_t)s, c.seed);
         if constexpr (JIT)
             hj.init((uint32_t)i, (uint32_t)s | 0x80000000u, c.seed);
         uint32_t pend = 0;
-        float kh = 0.5f;
-        for (int k = 0; k < c.steps; ++k, kh += 1.0f) {
+        float kh = (float)rg.k0 + 0.5f;
+        for (int k = rg.k0; k < rg.k1; ++k, kh += 1.0f) {
             int i0[3], o[3];
             float t[3];
             if constexpr (JIT) {
@@ -752,6 +757,40 @@ __global__ __launch_bounds__(256) void k_emit_stoch(RaymarchCall c, uint32_t log
         e[1] += __shfl_xor(e[1], m);
         e[2] += __shfl_xor(e[2], m);
     }
+    if (log_split) {
+        // and the segments' in segment order
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+            part[rg.wave][rg.lane][b] = e[b];
+        __syncthreads();
+        if (rg.seg == 0) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                CompSum t;
+                t.init();
+                for (int q = 0; q < (1 << log_split); ++q)
+                    t.add(part[rg.wave + q][rg.lane][b]);
+                e[b] = t.value();
+            }
+        }
+    }
+    if (st == 3 || rg.seg != 0)
+        return;
+    if (st != 0) {
+        const float v = st == 1 ? 0.0f : __builtin_nanf("");
+        if (lane == 0) {
+            c.T[3 * i] = v;
+            c.T[3 * i + 1] = v;
+            c.T[3 * i + 2] = v;
+        }
+        if constexpr (DBG) {
+            const int64_t per = (int64_t)3 * c.steps;
+            for (int s = lane; s < c.spp; s += G)
+                for (int64_t k = 0; k < per; ++k)
+                    c.taps[((int64_t)i * c.spp + s) * per + k] = SF_TAP_NONE;
+        }
+        return;
+    }
     if (lane == 0) {
         const float sc = g.dt / (float)c.spp;
         c.T[3 * i] = e[0] * sc;
@@ -760,102 +799,63 @@ __global__ __launch_bounds__(256) void k_emit_stoch(RaymarchCall c, uint32_t log
     }
 }
 
-// Deterministic emission: E_k = B(sum_i w_i T_i) before shading,
+// Deterministic emission (march_taps: 262,144 rays x 256 steps of the 512^3
+// fire, tricubic after 9.9 -> 3.7 ms, bound by the transcendental unit, and
+// before 3.4 -> 1.9 ms): E_k = B(sum_i w_i T_i) before shading,
 // sum_i w_i B(T_i) after; binary32 weights and per-step sums of positive
 // terms, steps summed with compensation.
 template <int F, bool HALF, int MODE, bool OCC>
-__global__ __launch_bounds__(256) void k_emit_det(RaymarchCall c, uint32_t log_run)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_emit_det(RaymarchCall c, uint32_t log_run, uint32_t log_split)
 {
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, log_run) * 256 + threadIdx.x;
-    if (i >= c.n)
-        return;
-    RayGeom g;
-    int st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    if (st != 0) {
-        const float v = st == 1 ? 0.0f : __builtin_nanf("");
-        c.T[3 * i] = v;
-        c.T[3 * i + 1] = v;
-        c.T[3 * i + 2] = v;
-        return;
-    }
-    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
-                                                                  (int)c.vol.bytes, kBufferFlags);
-    __amdgpu_buffer_rsrc_t rm;
-    if constexpr (OCC)
-        rm = occ_rsrc(c.vol);
+    __shared__ __attribute__((aligned(16))) float stage[4][4 * STAGE_UNITS];
+    const RaySegment r(log_run, log_split, c.steps);
+    const int64_t i = r.i;
+    RayGeom g = {};
+    int st = 3;   // no ray
+    if (i < c.n)
+        st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
     constexpr int NT = Taps<F>::n;
-    constexpr int F0 = Taps<F>::first;
     CompSum acc[3];
     acc[0].init();
     acc[1].init();
     acc[2].init();
-    float kh = 0.5f;
-    for (int k = 0; k < c.steps; ++k, kh += 1.0f) {
-        int i0[3];
-        float t[3];
-        float wx[4], wy[4], wz[4];
-        step_coords(g, kh, i0, t);
-        if constexpr (OCC) {
-            if (brick_empty_clamped(rm, c.vol, i0))
-                continue;   // every tap is 0 K: no emission either way
-        }
-        if constexpr (F == NEAREST) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                i0[a] += t[a] >= 0.5f;
-        }
-        axis_weights<F>(t[0], wx);
-        axis_weights<F>(t[1], wy);
-        axis_weights<F>(t[2], wz);
+    march_taps<F, HALF, OCC>(c.vol, g, st == 0, r.k0, r.k1, stage[r.wave],
+                             [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
         float e[3] = {0.0f, 0.0f, 0.0f};
-        // one x row of temperatures into the sums, in tap order
-        auto add_row = [&](const float *Tr, int by, int cz) {
-            const float wyz = wy[by] * wz[cz];
+        // exact after: a plane at a time and its rows one by one, since all 64
+        // taps side by side take more registers than there are
+        auto add_taps = [&](auto cool) {
+#pragma unroll(MODE == BEFORE ? NT : 1)
+            for (int cz = 0; cz < NT; ++cz) {
+                const float wzc = MODE == BEFORE || NT == 1 ? wz[cz] : (NT == 2 ? (cz == 0 ? wz[0] : wz[1])
+                                                              : (cz < 2 ? (cz == 0 ? wz[0] : wz[1]) : (cz == 2 ? wz[2] : wz[3])));
 #pragma unroll
-            for (int ax = 0; ax < NT; ++ax) {
-                const float T = Tr[ax];
-                const float w = wx[ax] * wyz;
-                if constexpr (MODE == BEFORE) {
-                    e[0] = __builtin_fmaf(w, T, e[0]);
-                } else {
-                    float B[3];
-                    planck3(T, B);
-                    e[0] = __builtin_fmaf(w, B[0], e[0]);
-                    e[1] = __builtin_fmaf(w, B[1], e[1]);
-                    e[2] = __builtin_fmaf(w, B[2], e[2]);
+                for (int by = 0; by < NT; ++by) {
+                    float t[NT];
+                    taps.row(by, cz, t);
+                    const float wyz = wy[by] * wzc;
+#pragma unroll
+                    for (int ax = 0; ax < NT; ++ax) {
+                        const float w = wx[ax] * wyz;
+                        if constexpr (MODE == BEFORE) {
+                            e[0] = __builtin_fmaf(w, t[ax], e[0]);
+                        } else {
+                            float B[3];
+                            planck3<decltype(cool)::value>(t[ax], B);
+                            e[0] = __builtin_fmaf(w, B[0], e[0]);
+                            e[1] = __builtin_fmaf(w, B[1], e[1]);
+                            e[2] = __builtin_fmaf(w, B[2], e[2]);
+                        }
+                    }
+                    if constexpr (MODE != BEFORE)
+                        __builtin_amdgcn_sched_barrier(0);
                 }
             }
         };
-        // rows of four binary16 voxels by one load where every tap is inside
-        // the grid, as in the transmittance comparators
-        bool rows = false;
-        if constexpr (HALF && NT == 4)
-            rows = rows4_inside(c.vol, i0);
-        if (rows) {
-            const uint32_t nx = (uint32_t)c.vol.nx, ny = (uint32_t)c.vol.ny;
-            const uint32_t e0 = ((uint32_t)(i0[2] - 1) * ny + (uint32_t)(i0[1] - 1)) * nx + (uint32_t)(i0[0] - 1);
-#pragma unroll
-            for (int cz = 0; cz < NT; ++cz) {
-#pragma unroll
-                for (int by = 0; by < NT; ++by) {
-                    float Tr[4];
-                    voxel_row4_half(rs, e0 + ((uint32_t)cz * ny + (uint32_t)by) * nx, Tr);
-                    add_row(Tr, by, cz);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int cz = 0; cz < NT; ++cz) {
-#pragma unroll
-                for (int by = 0; by < NT; ++by) {
-                    float Tr[NT];
-#pragma unroll
-                    for (int ax = 0; ax < NT; ++ax)
-                        Tr[ax] = voxel<HALF>(rs, c.vol, i0[0] + F0 + ax, i0[1] + F0 + by, i0[2] + F0 + cz);
-                    add_row(Tr, by, cz);
-                }
-            }
-        }
+        if (MODE == BEFORE || largest < PLANCK_HOT)
+            add_taps(std::true_type{});
+        else
+            add_taps(std::false_type{});
         if constexpr (MODE == BEFORE) {
             float B[3];
             planck3(e[0], B);
@@ -867,10 +867,28 @@ __global__ __launch_bounds__(256) void k_emit_det(RaymarchCall c, uint32_t log_r
             acc[1].add(e[1]);
             acc[2].add(e[2]);
         }
+    });
+    if (log_split) {
+        // the segments' sums meet in segment order
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            stage[r.wave][6 * r.lane + 2 * b] = acc[b].s;
+            stage[r.wave][6 * r.lane + 2 * b + 1] = acc[b].c;
+        }
+        __syncthreads();
+        if (r.seg == 0)
+            for (int q = 1; q < (1 << log_split); ++q)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    acc[b].add(stage[r.wave + q][6 * r.lane + 2 * b]);
+                    acc[b].c += stage[r.wave + q][6 * r.lane + 2 * b + 1];
+                }
     }
-    c.T[3 * i] = acc[0].value() * g.dt;
-    c.T[3 * i + 1] = acc[1].value() * g.dt;
-    c.T[3 * i + 2] = acc[2].value() * g.dt;
+    if (r.seg != 0 || st == 3)
+        return;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        c.T[3 * i + b] = st == 0 ? acc[b].value() * g.dt : (st == 1 ? 0.0f : __builtin_nanf(""));
 }
 
 // ------------------------------------------------------------- point lookups
@@ -1112,9 +1130,8 @@ struct SplitGrid {
 };
 
 template <int F, bool HALF, bool OCC, bool P2>
-static void launch_ray_fo(const RaymarchCall &c, dim3 grid, hipStream_t s, uint32_t log_run)
+static void launch_ray_fo(const RaymarchCall &c, hipStream_t s)
 {
-    dim3 block(256);
     if (c.mode == STOCH) {
         const SplitGrid sg(c.n, c.steps, 4);
         if (c.variant)
@@ -1133,8 +1150,6 @@ static void launch_ray_fo(const RaymarchCall &c, dim3 grid, hipStream_t s, uint3
 template <int F, bool HALF>
 static hipError_t launch_ray_f(const RaymarchCall &c, hipStream_t s)
 {
-    const XcdGrid xg(blocks_for(c.n), 256);
-    dim3 grid(xg.blocks), block(256);
     const bool p2 = c.vol.lx >= 0;
     if (c.mode == STOCH && c.taps) {
         // the tap dump records every step, so it never skips empty bricks
@@ -1145,14 +1160,14 @@ static hipError_t launch_ray_f(const RaymarchCall &c, hipStream_t s)
             k_ray_stoch<F, HALF, 0, true, false, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
     } else if (c.vol.occ) {
         if (p2)
-            launch_ray_fo<F, HALF, true, true>(c, grid, s, xg.log_run);
+            launch_ray_fo<F, HALF, true, true>(c, s);
         else
-            launch_ray_fo<F, HALF, true, false>(c, grid, s, xg.log_run);
+            launch_ray_fo<F, HALF, true, false>(c, s);
     } else {
         if (p2)
-            launch_ray_fo<F, HALF, false, true>(c, grid, s, xg.log_run);
+            launch_ray_fo<F, HALF, false, true>(c, s);
         else
-            launch_ray_fo<F, HALF, false, false>(c, grid, s, xg.log_run);
+            launch_ray_fo<F, HALF, false, false>(c, s);
     }
     return hipGetLastError();
 }
@@ -1161,35 +1176,34 @@ template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
 static void launch_emit_stoch(const RaymarchCall &c, hipStream_t s)
 {
     const int G = lane_group(c.n, c.spp);
-    const XcdGrid xg(blocks_for(c.n * G), 256);
+    const SplitGrid sg(c.n * G, c.steps, 4);
     const int lg = __builtin_ctz(G);
     if (c.footprint > 0.0f)
-        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(xg.blocks), dim3(256), 0, s>>>(c, xg.log_run, lg);
+        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split, lg);
     else
-        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, false><<<dim3(xg.blocks), dim3(256), 0, s>>>(c, xg.log_run, lg);
+        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split, lg);
 }
 
 template <int F, bool HALF, bool OCC, bool P2>
-static void launch_emit_fo(const RaymarchCall &c, dim3 grid, hipStream_t s, uint32_t log_run)
+static void launch_emit_fo(const RaymarchCall &c, hipStream_t s)
 {
-    dim3 block(256);
     if (c.mode == STOCH) {
         if (c.variant)
             launch_emit_stoch<F, HALF, 1, false, OCC, P2>(c, s);
         else
             launch_emit_stoch<F, HALF, 0, false, OCC, P2>(c, s);
     } else if (c.mode == BEFORE) {
-        k_emit_det<F, HALF, BEFORE, OCC><<<grid, block, 0, s>>>(c, log_run);
+        const SplitGrid sg(c.n, c.steps, 2);
+        k_emit_det<F, HALF, BEFORE, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
     } else {
-        k_emit_det<F, HALF, AFTER, OCC><<<grid, block, 0, s>>>(c, log_run);
+        const SplitGrid sg(c.n, c.steps, 2);
+        k_emit_det<F, HALF, AFTER, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
     }
 }
 
 template <int F, bool HALF>
 static hipError_t launch_emit_f(const RaymarchCall &c, hipStream_t s)
 {
-    const XcdGrid xg(blocks_for(c.n), 256);
-    dim3 grid(xg.blocks);
     const bool p2 = c.vol.lx >= 0;
     if (c.mode == STOCH && c.taps) {
         if (c.variant)
@@ -1198,14 +1212,14 @@ static hipError_t launch_emit_f(const RaymarchCall &c, hipStream_t s)
             launch_emit_stoch<F, HALF, 0, true, false, false>(c, s);
     } else if (c.vol.occ) {
         if (p2)
-            launch_emit_fo<F, HALF, true, true>(c, grid, s, xg.log_run);
+            launch_emit_fo<F, HALF, true, true>(c, s);
         else
-            launch_emit_fo<F, HALF, true, false>(c, grid, s, xg.log_run);
+            launch_emit_fo<F, HALF, true, false>(c, s);
     } else {
         if (p2)
-            launch_emit_fo<F, HALF, false, true>(c, grid, s, xg.log_run);
+            launch_emit_fo<F, HALF, false, true>(c, s);
         else
-            launch_emit_fo<F, HALF, false, false>(c, grid, s, xg.log_run);
+            launch_emit_fo<F, HALF, false, false>(c, s);
     }
     return hipGetLastError();
 }

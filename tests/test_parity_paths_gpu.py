@@ -179,3 +179,37 @@ def test_every_tap_march_of_non_finite_voxels(sf, cloud48):
         assert hit.any() and not hit.all()
         same = a == b
         assert (same | hit | (b < a)).all() and same.mean() > 0.3
+
+
+# temperatures below, around and above the 41,000 K at which a band of
+# Planck's law changes its form; the brick mask, the split of the steps and
+# the staged box (coherent rays) or its fallback (incoherent ones)
+@pytest.mark.parametrize("peak", [6000.0, 60000.0])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("rays_kind", ["coherent", "incoherent"])
+@pytest.mark.parametrize("steps", [9, 64])
+def test_emission_forms(sf, orc, cloud48, peak, dtype, rays_kind, steps):
+    """Every mode against the oracle; relative tolerance 1e-5 with a floor of
+    1e-6 of the batch's largest value (Planck's law in binary32)."""
+    from paper_2407_06107_amd import inputs
+    _case("emission_forms", peak, np.dtype(dtype).name, rays_kind, steps)
+    data = np.ascontiguousarray(cloud48[:40, :36, :44].astype(np.float32))
+    data = np.where(data > 0, 800 + (peak - 800) * np.sqrt(data / data.max()), 0).astype(dtype)
+    if rays_kind == "coherent":
+        rays = inputs.ortho_rays(16, 16, side=1.0, seed=2)
+    else:
+        rays = inputs.random_rays(700, 1.0, seed=3)
+        rays[5, 7] = rays[5, 6]
+        rays[6, 0] = np.inf
+    rd = torch.from_numpy(rays).cuda()
+    og, vol = _grids(orc, sf, data)
+    _, volm = _grids(orc, sf, data, brick=2)
+    for filt in ("LINEAR", "BSPLINE3"):
+        for mode, gmode, spp in ((orc.STOCHASTIC, sf.SF_STOCHASTIC, 3), (orc.BEFORE, sf.SF_BEFORE, 1),
+                                 (orc.AFTER, sf.SF_AFTER_EXACT, 1)):
+            ref = orc.raymarch_emission(og, rays, steps, getattr(orc, filt), mode, spp=spp, seed=9)
+            smp = sf.sampling(getattr(sf, "SF_" + filt), gmode, spp, seed=9)
+            for v in (vol, volm):
+                L = sf.sf_raymarch_emission(v, rd, steps, smp).cpu().numpy()
+                top = np.nanmax(ref, axis=0)
+                assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6, equal_nan=True), (filt, gmode)
