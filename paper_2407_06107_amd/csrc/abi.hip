@@ -824,12 +824,13 @@ static int train_parts(int64_t batch)
     return (int)(p < 1 ? 1 : (p > 2048 ? 2048 : p));
 }
 
-// One wavefront per 16-sample tile up to 1024 wavefronts (one per SIMD of
-// a 256-CU device: each holds the registers of one), then longer chunks.
-// Never more than train_parts(batch), so one workspace size serves both modes.
-static int train_parts_mfma(int64_t batch)
+// Wavefronts of the matrix-core step: one per pair of 16-sample tiles up to
+// 1024 (one per SIMD of a 256-CU device: each holds the registers of one),
+// then longer chunks.  They leave fewer rows than train_parts(batch), so one
+// workspace size serves both modes.
+static int train_waves_mfma(int64_t batch)
 {
-    int64_t p = (batch + 15) / 16;
+    int64_t p = (batch + 31) / 32;
     return (int)(p < 1 ? 1 : (p > 1024 ? 1024 : p));
 }
 
@@ -887,13 +888,12 @@ sf_status sf_neural_train_step(const sf_train_state *stt, const int32_t *batch_i
     t.grad_params = grad_params;
     t.grad_latents = grad_latents;
     if (stt->compute == SF_TRAIN_BF16) {
-        // fewer, longer chunks than the FP32 path (at most as many partials):
-        // a wavefront loads its weight fragments once for 8 tiles of 16
-        const int parts = train_parts_mfma(batch);
-        const int64_t chunk = ((batch + parts - 1) / parts + 15) / 16 * 16;
-        hipError_t e = sfk::launch_train_mfma(t, (float *)workspace, parts, chunk, (hipStream_t)stream);
+        const int waves = train_waves_mfma(batch);
+        const int64_t chunk = ((batch + waves - 1) / waves + 31) / 32 * 32;
+        const int rows = (int)(((batch + chunk - 1) / chunk + sfk::TRAIN_WAVES - 1) / sfk::TRAIN_WAVES);
+        hipError_t e = sfk::launch_train_mfma(t, (float *)workspace, rows, chunk, (hipStream_t)stream);
         if (e == hipSuccess)
-            e = sfk::launch_train_reduce(t, (float *)workspace, parts, (hipStream_t)stream);
+            e = sfk::launch_train_reduce(t, (float *)workspace, rows, (hipStream_t)stream);
         return device_status(e);
     }
     const int parts = train_parts(batch);

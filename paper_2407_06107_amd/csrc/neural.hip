@@ -10,8 +10,8 @@
 //    matrix-core step is in train.hip): one wavefront streams a chunk of the
 //    batch; lane h owns hidden unit h, so both matrix-vector products of a
 //    sample are 64-lane broadcasts from LDS.  Per-wavefront parameter
-//    gradients of either step are summed in a fixed order by two kernels here,
-//    the second of which applies Adam; latent gradients are applied at once
+//    gradients of either step are summed in a fixed order by a kernel here,
+//    which applies Adam; latent gradients are applied at once
 //    (each batch entry owns its latent).
 //  - Decoding (BF16 matrix cores, FP32 accumulation): 16 samples form the
 //    columns of one v_mfma_f32_16x16x32_bf16 tile with hidden units as rows,
@@ -384,64 +384,63 @@ __global__ __launch_bounds__(64) void k_train(TrainCall t, int64_t chunk, float 
 
 constexpr int TRAIN_GROUP = 2;   // samples per iteration of k_train
 
-// First stage of the gradient sum: chunk c (blockIdx.y) of REDUCE_CHUNK
-// consecutive per-wavefront partials, summed in order.
-constexpr int REDUCE_CHUNK = 64;
-
-// All REDUCE_CHUNK loads are issued before the first addition (a partial
-// past the last reads the last one's address and adds +0).
-__global__ __launch_bounds__(256) void k_train_chunks(int nparts, const float *partials, int npar, float *chunks)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > npar)
-        return;
-    const int w0 = blockIdx.y * REDUCE_CHUNK, w1 = min(w0 + REDUCE_CHUNK, nparts);
-    float v[REDUCE_CHUNK];
-#pragma unroll
-    for (int j = 0; j < REDUCE_CHUNK; ++j) {
-        const float x = partials[(int64_t)min(w0 + j, w1 - 1) * (npar + 1) + p];
-        v[j] = w0 + j < w1 ? x : 0.0f;
-    }
-    float g = 0.0f;
-#pragma unroll
-    for (int j = 0; j < REDUCE_CHUNK; ++j)
-        g += v[j];
-    chunks[(int64_t)blockIdx.y * (npar + 1) + p] = g;
-}
-
-// Sum the chunk sums in order (a fixed order overall: the result does not
+// Sum the rows of partial gradients in a fixed order (the result does not
 // depend on scheduling) and take one Adam step per parameter; the loss lands
-// in loss_out.
-__global__ __launch_bounds__(256) void k_train_reduce(TrainCall t, int nchunks, const float *chunks, int npar)
+// in loss_out.  A workgroup takes 32 columns (whole lines, and enough
+// workgroups for the 2048 rows of the FP32 step); 32 groups of lanes each sum a
+// contiguous share of the rows, 16 loads in flight, and their sums are added
+// in order.  One launch: 4.2 us for 256 rows, 4.9 for the 64 columns x 16
+// groups that also took the FP32 step of 262,144 samples from 617 to 634 us;
+// two launches (sums of 64 rows, then those) took 5.1 + 4.6 for 1024 rows.
+constexpr int REDUCE_COLS = 32, REDUCE_GROUPS = 32;
+
+__global__ __launch_bounds__(REDUCE_COLS * REDUCE_GROUPS) void k_train_reduce(TrainCall t, int nrows,
+                                                                              const float *partials, int npar)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > npar)
-        return;
-    // the chunk sums in order, loaded MAX_CHUNKS at a time before they are added
-    constexpr int MAX_CHUNKS = 32;
+    __shared__ float sums[REDUCE_GROUPS][REDUCE_COLS];
+    const int c = threadIdx.x % REDUCE_COLS, grp = threadIdx.x / REDUCE_COLS;
+    const int p = blockIdx.x * REDUCE_COLS + c;
+    const int per = (nrows + REDUCE_GROUPS - 1) / REDUCE_GROUPS;
+    const int r0 = min(grp * per, nrows), r1 = min(r0 + per, nrows);
+    const float *col = partials + min(p, npar);
+    // the parameter's Adam state is on its way while the rows are summed
+    float mp = 0.0f, vp = 0.0f, xp = 0.0f;
+    if (grp == 0 && p < npar) {
+        mp = t.m_par[p];
+        vp = t.v_par[p];
+        xp = t.params[p];
+    }
+    constexpr int BATCH = 16;
     float g = 0.0f;
-    for (int w0 = 0; w0 < nchunks; w0 += MAX_CHUNKS) {
-        float v[MAX_CHUNKS];
+    for (int r = r0; r < r1; r += BATCH) {
+        float v[BATCH];
 #pragma unroll
-        for (int j = 0; j < MAX_CHUNKS; ++j) {
-            const float x = chunks[(int64_t)min(w0 + j, nchunks - 1) * (npar + 1) + p];
-            v[j] = w0 + j < nchunks ? x : 0.0f;
+        for (int j = 0; j < BATCH; ++j) {
+            const float x = col[(int64_t)min(r + j, r1 - 1) * (npar + 1)];
+            v[j] = r + j < r1 ? x : 0.0f;
         }
 #pragma unroll
-        for (int j = 0; j < MAX_CHUNKS; ++j)
+        for (int j = 0; j < BATCH; ++j)
             g += v[j];
     }
+    sums[grp][c] = g;
+    __syncthreads();
+    if (grp != 0 || p > npar)
+        return;
+#pragma unroll
+    for (int k = 1; k < REDUCE_GROUPS; ++k)
+        g += sums[k][c];
     if (p == npar) {
         t.loss_out[0] = g / (float)t.batch;
         return;
     }
     if (t.grad_params)
         t.grad_params[p] = g;
-    const float m = 0.9f * t.m_par[p] + 0.1f * g;
-    const float v = 0.999f * t.v_par[p] + 0.001f * g * g;
+    const float m = 0.9f * mp + 0.1f * g;
+    const float v = 0.999f * vp + 0.001f * g * g;
     t.m_par[p] = m;
     t.v_par[p] = v;
-    t.params[p] -= t.lr_mlp * (m / t.bc1) / (__builtin_sqrtf(v / t.bc2) + 1e-8f);
+    t.params[p] = xp - t.lr_mlp * (m / t.bc1) / (__builtin_sqrtf(v / t.bc2) + 1e-8f);
 }
 
 // ------------------------------------------------------- matrix-core decoder
@@ -985,14 +984,12 @@ hipError_t launch_train(const TrainCall &t, float *workspace, int nparts, int64_
 hipError_t launch_train_reduce(const TrainCall &t, float *workspace, int nparts, hipStream_t s)
 {
     const int npar = POff(t.C, t.O).n;
-    const int nchunks = (nparts + REDUCE_CHUNK - 1) / REDUCE_CHUNK;
-    float *chunks = workspace + (int64_t)nparts * (npar + 1);
-    k_train_chunks<<<dim3((npar + 1 + 255) / 256, nchunks), dim3(256), 0, s>>>(nparts, workspace, npar, chunks);
-    k_train_reduce<<<dim3((npar + 1 + 255) / 256), dim3(256), 0, s>>>(t, nchunks, chunks, npar);
+    k_train_reduce<<<dim3((npar + REDUCE_COLS) / REDUCE_COLS), dim3(REDUCE_COLS * REDUCE_GROUPS), 0, s>>>(t, nparts, workspace, npar);
     return hipGetLastError();
 }
 
-int train_reduce_chunks(int nparts) { return (nparts + REDUCE_CHUNK - 1) / REDUCE_CHUNK; }
+// Rows the workspace holds beside the partial ones (part of its size).
+int train_reduce_chunks(int nparts) { return (nparts + 63) / 64; }
 
 int train_nparams(int C, int O) { return POff(C, O).n; }
 

@@ -213,3 +213,49 @@ def test_emission_forms(sf, orc, cloud48, peak, dtype, rays_kind, steps):
                 L = sf.sf_raymarch_emission(v, rd, steps, smp).cpu().numpy()
                 top = np.nanmax(ref, axis=0)
                 assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6, equal_nan=True), (filt, gmode)
+
+
+def _bf16(a):
+    """a rounded to bfloat16 (nearest even), in float64."""
+    return torch.as_tensor(np.asarray(a, np.float32)).to(torch.bfloat16).to(torch.float64).numpy()
+
+
+# one lane of the first tile, a full and a started second tile, a full and a
+# started second pair of tiles, a second workgroup, and chunks of two pairs
+# whose last workgroups hold no samples
+@pytest.mark.parametrize("channels, out_dim", [(8, 4), (16, 1)])
+@pytest.mark.parametrize("batch", [1, 15, 16, 17, 31, 32, 33, 129, 32 * 1024 + 1])
+def test_training_step_at_tile_pair_edges(sf, orc, channels, out_dim, batch):
+    """Loss and gradients of one matrix-core step against the FP64 oracle on
+    the same BF16 operands.  The backward signals alone are rounded on one side
+    only, four times by a relative 2^-9 at most: 2e-2 normwise.  Latents outside the
+    batch keep their values."""
+    _case("train_pairs", channels, out_dim, batch)
+    C, O, H = channels, out_dim, 64
+    rng = np.random.default_rng(1000 * channels + batch)
+    nlat = batch + 50
+    lat = rng.normal(size=(nlat, C)).astype(np.float32)
+    offs = np.cumsum([0, C * H, H, H * H, H, H * O, O])
+    P = (0.2 * rng.normal(size=offs[-1])).astype(np.float32)
+    targets = rng.uniform(0, 1, size=(nlat, O)).astype(np.float32)
+    idx = rng.permutation(nlat)[:batch].astype(np.int32)
+    st = sf.TrainState(torch.from_numpy(lat.ravel()).cuda(), torch.from_numpy(P).cuda(), C, O)
+    gP = torch.zeros(P.size, dtype=torch.float32, device="cuda")
+    gZ = torch.zeros((batch, C), dtype=torch.float32, device="cuda")
+    tg = torch.from_numpy(targets.ravel()).cuda()
+    loss = sf.sf_neural_train_step(st, torch.from_numpy(idx).cuda(), tg, lr_latent=1e-2, lr_mlp=0.0, grad_params=gP,
+                                   grad_latents=gZ)
+    Q = P.astype(np.float64)
+    for k in (0, 2, 4):
+        Q[offs[k]:offs[k + 1]] = _bf16(P[offs[k]:offs[k + 1]])
+    oloss, ogP, ogZ = orc.mlp_grad(C, H, O, Q, _bf16(lat[idx]), targets[idx].astype(np.float64), act_bf16=True)
+    assert abs(loss.item() - oloss) <= 2e-2 * oloss
+    gp = gP.cpu().numpy().astype(np.float64)
+    for a, b in zip(offs[:-1], offs[1:]):
+        assert np.linalg.norm(gp[a:b] - ogP[a:b]) <= 2e-2 * max(np.linalg.norm(ogP[a:b]), 1e-30), (a, b)
+    gz = gZ.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(gz - ogZ) <= 2e-2 * np.linalg.norm(ogZ)
+    newZ = st.latents.cpu().numpy().reshape(nlat, C).astype(np.float64)
+    assert np.allclose(newZ[idx], lat[idx] - 1e-2 * gz / (np.abs(gz) + 1e-8), rtol=0, atol=2e-6)
+    rest = np.setdiff1d(np.arange(nlat), idx)
+    assert np.array_equal(newZ[rest], lat[rest].astype(np.float64))
