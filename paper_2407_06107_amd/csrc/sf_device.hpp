@@ -236,10 +236,8 @@ __device__ __forceinline__ float log2c(float x)
 
 // e^x, x in [-80, 0] (0 below): n = floor(x log2 e + 1/2), r = x - n ln 2
 // (two parts), Taylor polynomial of e^r to r^7, scaled by 2^n.
-__device__ __forceinline__ float expc(float x)
+__device__ __forceinline__ float expc_near(float x)   // x not below -80
 {
-    if (!(x >= -80.0f))
-        return 0.0f;
     const float n = __builtin_floorf(__builtin_fmaf(x, 1.44269504f, 0.5f));
     float r = __builtin_fmaf(-n, LN2_HI, x);
     r = __builtin_fmaf(-n, LN2_LO, r);
@@ -251,6 +249,11 @@ __device__ __forceinline__ float expc(float x)
     p = __builtin_fmaf(r, p, 1.0f);
     p = __builtin_fmaf(r, p, 1.0f);
     return __builtin_ldexpf(p, (int)n);
+}
+
+__device__ __forceinline__ float expc(float x)
+{
+    return x >= -80.0f ? expc_near(x) : 0.0f;
 }
 
 // cos and sin of 2 pi v, v in [0, 1): quadrant from 4v (exact), the rest

@@ -259,3 +259,29 @@ def test_training_step_at_tile_pair_edges(sf, orc, channels, out_dim, batch):
     assert np.allclose(newZ[idx], lat[idx] - 1e-2 * gz / (np.abs(gz) + 1e-8), rtol=0, atol=2e-6)
     rest = np.setdiff1d(np.arange(nlat), idx)
     assert np.array_equal(newZ[rest], lat[rest].astype(np.float64))
+
+
+# half-extents in rows: a single run of rows per mark, 16 marks just full, the
+# first sizes with two and with four rows a mark, and wider than the limit
+@pytest.mark.parametrize("half", [0.4, 2.0, 6.4, 7.3, 7.9, 8.4, 15.5, 16.5, 33.0, 90.0])
+@pytest.mark.parametrize("spp", [1, 5])
+def test_ewa_pick_over_runs_of_rows(sf, orc, half, spp):
+    """The picked texel is the oracle's, bit for bit, however the rows of the
+    footprint's box are grouped, for upright and slanted footprints, also where
+    the uniform is so large that the last texel is taken."""
+    _case("ewa_runs", half, spp)
+    rng = np.random.default_rng(int(10 * half))
+    lv = _pyramid(96, 384, 7)
+    n = 1500
+    q = np.zeros((n, 6), np.float32)
+    q[:, :2] = rng.uniform(-0.2, 1.2, (n, 2))
+    q[:, 2] = rng.uniform(0.9, 1.9, n) / 96                       # about a texel along x
+    q[:, 5] = half * rng.uniform(0.97, 1.03, n) / 384
+    q[::3, 4] = rng.uniform(-0.7, 0.7, len(q[::3])) * half / 96   # slanted
+    ot, gt = _filter_case(orc, sf, lv, "REPEAT", True)
+    smp = sf.sampling(sf.SF_EWA, sf.SF_STOCHASTIC, spp, seed=5)
+    taps = torch.full((n, spp, 3), 99, dtype=torch.int32, device="cuda")
+    out = sf.sf_filter2d_aniso(gt, torch.from_numpy(q).cuda(), smp, aniso_max=16, dbg_taps=taps)
+    ref, rt = orc.filter2d_aniso(ot, q, orc.EWA, orc.STOCHASTIC, spp=spp, seed=5, taps=True, amax=16)
+    assert np.array_equal(taps.cpu().numpy(), rt)
+    assert np.allclose(out.cpu().numpy(), ref, rtol=0, atol=1e-6)   # a mean of at most 5 exact texels
