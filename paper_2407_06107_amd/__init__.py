@@ -165,8 +165,11 @@ def _ptr(t):
 
 
 def _stream(stream):
+    """The stream's handle, by default the current device's current stream's
+    (the handle alone: a ``torch.cuda.Stream`` object round it takes 2.8 us to
+    make, the handle 0.2 us, and a small launch 8 us in all)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return C.c_void_p(stream.cuda_stream)
 
 
