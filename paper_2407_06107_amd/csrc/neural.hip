@@ -23,6 +23,7 @@
 
 #include "sf_device.hpp"
 #include "sf_internal.hpp"
+#include "tex2d.hpp"
 #include "volume_dev.hpp"
 
 #pragma clang fp contract(off)
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256) void k_quant_fp8(const float *lat, LatentArgs 
 // Packed parameter offsets: W1 [C x H], b1 [H], W2 [H x H], b2 [H], W3 [H x O], b3 [O].
 struct POff {
     int w1, b1, w2, b2, w3, b3, n;
-    __host__ __device__ POff(int C, int O)
+    __host__ __device__ constexpr POff(int C, int O) : w1(0), b1(0), w2(0), b2(0), w3(0), b3(0), n(0)
     {
         w1 = 0;
         b1 = C * HID;
@@ -460,39 +461,99 @@ struct MlpFrags {
     f32x4 b1[4], b2[4], b3;
 };
 
-__device__ __forceinline__ float pbf(const uint16_t *P, int i) { return bf16_bits_to_f32(P[i]); }
+// The packed parameters in LDS, rows of 64 on 68 values (8-byte aligned, and
+// the transposing read's four rows in different banks), W1 with zero rows up to
+// the 16 inputs of its tile.
+constexpr int FRAG_ROW = HID + 4;
 
+template <int C, int O>
+struct FragLds {
+    uint16_t w1[16 * FRAG_ROW], w2[HID * FRAG_ROW], w3[HID * O], b1[HID], b2[HID], b3[O];
+};
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Rows r..r+3 (r = first + 4g) of column f0 + n of a matrix in LDS: the
+// transposing read hands lane n of a group of 16 column n of the four rows that
+// the group's lanes address in quarters.
+__device__ __forceinline__ bf16x4 frag_col(const uint16_t *w, int first, int f0)
+{
+    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
+    const uint16_t *p = w + (first + 4 * g + (n >> 2)) * FRAG_ROW + f0 + 4 * (n & 3);
+    return __builtin_bit_cast(
+        bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p));
+}
+
+// A workgroup of 256 brings the parameters in by whole lines and each wavefront
+// takes its fragments from LDS by transposing reads (gathered from memory they
+// were 132 two-byte loads a lane; a march of 64 x 64 rays took 154 us, now 139).  The output layer's rows repeat: row r
+// holds output r mod 4 (the last one past O), so that the lanes of every K block
+// hold their sample's outputs.
 template <int C, int O>
 __device__ __forceinline__ void load_frags(const uint16_t *P, MlpFrags<C, O> &F)
 {
-    const POff off(C, O);
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
+    __shared__ __attribute__((aligned(16))) FragLds<C, O> sh;
+    constexpr POff off(C, O);
+    constexpr int N1 = C * HID / 256, N2 = HID * HID / 256, REST = off.n - off.b2 + HID, NR = (REST + 255) / 256;
+    const int t = threadIdx.x;
+    {
+        uint16_t w1[N1], w2[N2], r[NR];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+        for (int k = 0; k < N1; ++k)
+            w1[k] = P[off.w1 + t + 256 * k];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = 4 * g + j;
-            F.a1[m][j] = (__bf16)(c < C ? pbf(P, off.w1 + c * HID + 16 * m + n) : 0.0f);
+        for (int k = 0; k < N2; ++k)
+            w2[k] = P[off.w2 + t + 256 * k];
+        // b1, then b2, W3 and b3
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = min(t + 256 * k, REST - 1);
+            r[k] = P[i < HID ? off.b1 + i : off.b2 + i - HID];
         }
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int k = 0; k < 16 * HID / 256; ++k)
+            sh.w1[(t / HID + 4 * k) * FRAG_ROW + t % HID] = k < N1 ? w1[k < N1 ? k : 0] : (uint16_t)0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                F.a2[m][ks][j] = (__bf16)pbf(P, off.w2 + kperm(ks, g, j) * HID + 16 * m + n);
+        for (int k = 0; k < N2; ++k)
+            sh.w2[(t / HID + 4 * k) * FRAG_ROW + t % HID] = w2[k];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = t + 256 * k;
+            if (i < HID)
+                sh.b1[i] = r[k];
+            else if (i < 2 * HID)
+                sh.b2[i - HID] = r[k];
+            else if (i < 2 * HID + HID * O)
+                sh.w3[i - 2 * HID] = r[k];
+            else if (i < REST)
+                sh.b3[i - 2 * HID - HID * O] = r[k];
+        }
+    }
+    __syncthreads();
+    const int l = t & 63, n = l & 15, g = l >> 4, o = min(n & 3, O - 1);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        F.a1[m] = frag_col(sh.w1, 0, 16 * m);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint2 x = __builtin_bit_cast(uint2, frag_col(sh.w2, 32 * ks, 16 * m));
+            const uint2 y = __builtin_bit_cast(uint2, frag_col(sh.w2, 32 * ks + 16, 16 * m));
+            F.a2[m][ks] = __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, y.x, y.y));
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            F.b1[m][j] = pbf(P, off.b1 + 16 * m + 4 * g + j);
-            F.b2[m][j] = pbf(P, off.b2 + 16 * m + 4 * g + j);
+            F.b1[m][j] = bf16_bits_to_f32(sh.b1[16 * m + 4 * g + j]);
+            F.b2[m][j] = bf16_bits_to_f32(sh.b2[16 * m + 4 * g + j]);
         }
     }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            F.a3[ks][j] = (__bf16)(n < O ? pbf(P, off.w3 + kperm(ks, g, j) * O + n) : 0.0f);
+            F.a3[ks][j] = __builtin_bit_cast(__bf16, sh.w3[kperm(ks, g, j) * O + o]);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        F.b3[j] = (4 * g + j < O) ? pbf(P, off.b3 + 4 * g + j) : 0.0f;
+        F.b3[j] = bf16_bits_to_f32(sh.b3[min(j, O - 1)]);
 }
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));
@@ -534,8 +595,8 @@ __device__ __forceinline__ bf16x4 fp8x4_dequant(uint32_t w, float s)
 
 // The MLP on the 16 samples whose latents (K block of this lane, BF16, E4M3
 // latents already scaled) are in zb; each layer's bias enters its matrix
-// product as the accumulator.  Returns the layer-3 accumulators: lanes
-// 0..15 hold outputs 0..3 of sample (lane).
+// product as the accumulator.  Returns the layer-3 accumulators: outputs 0..3
+// of sample l % 16 in every lane l.
 template <int C, int O>
 __device__ __forceinline__ f32x4 mlp16(const MlpFrags<C, O> &F, bf16x4 zb)
 {
@@ -601,11 +662,8 @@ __device__ __forceinline__ void decode_wave(const LatentArgs &g, const MlpFrags<
     for (int G = 0; G < 4; ++G) {
         const f32x4 d3 = mlp16<C, O>(F, zb[G]);
 #pragma unroll
-        for (int o = 0; o < O; ++o) {
-            const float v = __shfl(d3[o], lane & 15);
-            if ((lane >> 4) == G)
-                y[o] = v;
-        }
+        for (int o = 0; o < O; ++o)
+            y[o] = G == 0 || (lane >> 4) == G ? d3[o] : y[o];
     }
 }
 
@@ -616,9 +674,9 @@ __device__ __forceinline__ int wrapi(int i, int n)
 }
 
 // 2-D neural texture lookups (repeat wrap).  Decoded texel = clamp(MLP, 0, 1).
-// One query per lane: filter the decoded latent texture at query q (every
-// lane of the wave takes part in the decodes; q >= n marks a lane with
-// nothing to do).
+// One query per lane: filter the decoded latent texture at query q over every
+// tap (every lane of the wave takes part in the decodes; q >= n marks a lane
+// with nothing to do).
 template <int F_, int SHADE, int MODE, int FMT>
 __device__ __forceinline__ void neural2d_query(const NeuralCall &c, const MlpFrags<8, 4> &Fr, int64_t q)
 {
@@ -644,82 +702,42 @@ __device__ __forceinline__ void neural2d_query(const NeuralCall &c, const MlpFra
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float y[O];
-    if constexpr (MODE == STOCH) {
-        for (int s = 0; s < c.spp; ++s) {
-            int64_t idx = -1;
-            int blk = 0;
-            if (ok) {
-                const uint4 w = pcg4d(make_uint4((uint32_t)q, (uint32_t)s, 0u, c.seed));
-                const int x = wrapi(ix + pick_off_2p24<F_>(tx, u24i(w.x)), R0);
-                const int yy = wrapi(iy + pick_off_2p24<F_>(ty, u24i(w.y)), R1);
-                idx = (int64_t)yy * R0 + x;
-                blk = c.lat.block_at(x, yy, 0);
-                if (c.taps) {
-                    c.taps[(q * c.spp + s) * 2] = x;
-                    c.taps[(q * c.spp + s) * 2 + 1] = yy;
-                }
-            } else if (active && c.taps) {
-                c.taps[(q * c.spp + s) * 2] = c.taps[(q * c.spp + s) * 2 + 1] = SF_TAP_NONE;
-            }
-            decode_wave<C, O, FMT>(c.lat, Fr, idx, blk, y);
+    constexpr int NT = Taps<F_>::n;
+    constexpr int F0 = Taps<F_>::first;
+    float wx[4], wy[4];
+    axis_weights<F_>(tx, wx);
+    axis_weights<F_>(ty, wy);
+    if constexpr (F_ == NEAREST) {
+        ix += tx >= 0.5f;
+        iy += ty >= 0.5f;
+    }
+    for (int b = 0; b < NT; ++b)
+        for (int a = 0; a < NT; ++a) {
+            const int xx = wrapi(ix + F0 + a, R0), yy = wrapi(iy + F0 + b, R1);
+            const int64_t idx = ok ? (int64_t)yy * R0 + xx : -1;
+            decode_wave<C, O, FMT>(c.lat, Fr, idx, c.lat.block_at(xx, yy, 0), y);
+            const float w = wx[a] * wy[b];
             float4 d = make_float4(__builtin_fminf(__builtin_fmaxf(y[0], 0.f), 1.f),
                                    __builtin_fminf(__builtin_fmaxf(y[1], 0.f), 1.f),
                                    __builtin_fminf(__builtin_fmaxf(y[2], 0.f), 1.f),
                                    __builtin_fminf(__builtin_fmaxf(y[3], 0.f), 1.f));
-            if constexpr (SHADE == SF_SHADE_GGX) {
+            if (MODE == AFTER && SHADE == SF_SHADE_GGX) {
                 const float3 r = shade_ggx_dev(c.g, d);
-                acc[0] += r.x;
-                acc[1] += r.y;
-                acc[2] += r.z;
+                acc[0] = __builtin_fmaf(w, r.x, acc[0]);
+                acc[1] = __builtin_fmaf(w, r.y, acc[1]);
+                acc[2] = __builtin_fmaf(w, r.z, acc[2]);
             } else {
-                acc[0] += d.x;
-                acc[1] += d.y;
-                acc[2] += d.z;
-                acc[3] += d.w;
+                acc[0] = __builtin_fmaf(w, d.x, acc[0]);
+                acc[1] = __builtin_fmaf(w, d.y, acc[1]);
+                acc[2] = __builtin_fmaf(w, d.z, acc[2]);
+                acc[3] = __builtin_fmaf(w, d.w, acc[3]);
             }
         }
-        const float inv = 1.0f / (float)c.spp;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            acc[k] *= inv;
-    } else {
-        constexpr int NT = Taps<F_>::n;
-        constexpr int F0 = Taps<F_>::first;
-        float wx[4], wy[4];
-        axis_weights<F_>(tx, wx);
-        axis_weights<F_>(ty, wy);
-        if constexpr (F_ == NEAREST) {
-            ix += tx >= 0.5f;
-            iy += ty >= 0.5f;
-        }
-        for (int b = 0; b < NT; ++b)
-            for (int a = 0; a < NT; ++a) {
-                const int xx = wrapi(ix + F0 + a, R0), yy = wrapi(iy + F0 + b, R1);
-                const int64_t idx = ok ? (int64_t)yy * R0 + xx : -1;
-                decode_wave<C, O, FMT>(c.lat, Fr, idx, c.lat.block_at(xx, yy, 0), y);
-                const float w = wx[a] * wy[b];
-                float4 d = make_float4(__builtin_fminf(__builtin_fmaxf(y[0], 0.f), 1.f),
-                                       __builtin_fminf(__builtin_fmaxf(y[1], 0.f), 1.f),
-                                       __builtin_fminf(__builtin_fmaxf(y[2], 0.f), 1.f),
-                                       __builtin_fminf(__builtin_fmaxf(y[3], 0.f), 1.f));
-                if (MODE == AFTER && SHADE == SF_SHADE_GGX) {
-                    const float3 r = shade_ggx_dev(c.g, d);
-                    acc[0] = __builtin_fmaf(w, r.x, acc[0]);
-                    acc[1] = __builtin_fmaf(w, r.y, acc[1]);
-                    acc[2] = __builtin_fmaf(w, r.z, acc[2]);
-                } else {
-                    acc[0] = __builtin_fmaf(w, d.x, acc[0]);
-                    acc[1] = __builtin_fmaf(w, d.y, acc[1]);
-                    acc[2] = __builtin_fmaf(w, d.z, acc[2]);
-                    acc[3] = __builtin_fmaf(w, d.w, acc[3]);
-                }
-            }
-        if (MODE == BEFORE && SHADE == SF_SHADE_GGX) {
-            const float3 r = shade_ggx_dev(c.g, make_float4(acc[0], acc[1], acc[2], acc[3]));
-            acc[0] = r.x;
-            acc[1] = r.y;
-            acc[2] = r.z;
-        }
+    if (MODE == BEFORE && SHADE == SF_SHADE_GGX) {
+        const float3 r = shade_ggx_dev(c.g, make_float4(acc[0], acc[1], acc[2], acc[3]));
+        acc[0] = r.x;
+        acc[1] = r.y;
+        acc[2] = r.z;
     }
     if (!active)
         return;
@@ -735,19 +753,175 @@ __device__ __forceinline__ void neural2d_query(const NeuralCall &c, const MlpFra
     }
 }
 
-// The MLP's fragments are loaded into registers once per workgroup, which
-// then walks the query stream in tiles of 256 (a grid of as many
-// workgroups as the device holds at once), so their load is spread over
-// several tiles.  The tile base is uniform over the workgroup.
+// One query's place: the lattice cell its filter sits on.
+struct Query2 {
+    bool active, ok;
+    int ix, iy;
+    float tx, ty;
+};
 
-template <int F_, int SHADE, int MODE, int FMT>
-__global__ __launch_bounds__(256) void k_neural2d(NeuralCall c)
+__device__ __forceinline__ float2 query_at(const NeuralCall &c, int64_t q)
 {
-    MlpFrags<8, 4> Fr;
-    load_frags<8, 4>(static_cast<const uint16_t *>(c.mlp.params), Fr);
+    return q < c.n ? make_float2(c.q[3 * q], c.q[3 * q + 1]) : make_float2(0.0f, 0.0f);
+}
+
+__device__ __forceinline__ Query2 place_query(const NeuralCall &c, int64_t q, float2 p)
+{
+    Query2 r;
+    r.active = q < c.n;
+    r.ok = r.active && __builtin_isfinite(p.x) && __builtin_isfinite(p.y);
+    const float u = p.x - __builtin_floorf(p.x), v = p.y - __builtin_floorf(p.y);
+    const float px = __builtin_fmaf(u, (float)c.lat.res[0], -0.5f), py = __builtin_fmaf(v, (float)c.lat.res[1], -0.5f);
+    const float fx = __builtin_floorf(px), fy = __builtin_floorf(py);
+    r.ix = r.ok ? (int)fx : 0;
+    r.iy = r.ok ? (int)fy : 0;
+    r.tx = px - fx;
+    r.ty = py - fy;
+    return r;
+}
+
+// i mod n for i within two of [0, n): one period up or down (n = 1: 0).
+__device__ __forceinline__ int wrap_near(int i, int n)
+{
+    const int r = i < 0 ? i + n : (i >= n ? i - n : i);
+    return min(max(r, 0), n - 1);
+}
+
+// The latents of one sample per lane, on their way: this lane's K block of the
+// four groups' samples, and the lane's own block scale (E4M3 latents).
+template <int FMT>
+struct Latents2 {
+    typename std::conditional<FMT == SF_LATENT_BF16, uint2, uint32_t>::type raw[4];
+    float cs;
+};
+
+template <int C, int FMT>
+__device__ __forceinline__ void issue_latents2(const LatentArgs &g, int64_t idx, int blk, Latents2<FMT> &L)
+{
+    typedef typename std::conditional<FMT == SF_LATENT_BF16, uint2, uint32_t>::type Raw;
+    const int lane = threadIdx.x & 63, kb = lane >> 4;
+    if constexpr (FMT != SF_LATENT_BF16)
+        L.cs = g.scales[blk];
+#pragma unroll
+    for (int G = 0; G < 4; ++G) {
+        const int src = 16 * G + (lane & 15);
+        const int64_t at = ((int64_t)__shfl((int)(idx >> 32), src) << 32) | (uint32_t)__shfl((int)idx, src);
+        L.raw[G] = Raw{};
+        if (4 * kb < C)
+            L.raw[G] = static_cast<const Raw *>(g.latents)[at * (C / 4) + kb];
+    }
+}
+
+template <int C, int O, int FMT>
+__device__ __forceinline__ void decode_latents2(const MlpFrags<C, O> &F, const Latents2<FMT> &L, float y[O])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int G = 0; G < 4; ++G) {
+        bf16x4 zb;
+        if constexpr (FMT == SF_LATENT_BF16)
+            zb = __builtin_bit_cast(bf16x4, L.raw[G]);
+        else
+            zb = fp8x4_dequant(L.raw[G], __shfl(L.cs, 16 * G + (lane & 15)));
+        const f32x4 d3 = mlp16<C, O>(F, zb);
+#pragma unroll
+        for (int o = 0; o < O; ++o)
+            y[o] = G == 0 || (lane >> 4) == G ? d3[o] : y[o];
+    }
+}
+
+// A workgroup takes the MLP's fragments into registers once and walks the
+// query stream in tiles of 256 (a grid of as many workgroups as the device
+// holds at once).  The tile base is uniform over the workgroup.
+//
+// Stochastic: a wavefront's tile is a chain (coordinates from memory, the pick,
+// the latents from memory, the MLP, the shading), so the chains of successive
+// samples overlap: the coordinates two tiles ahead and the latents of the next
+// sample are on their way while the MLP of this one runs.  (A lane without a
+// sample decodes a lattice point too; the result is not used.)  What bounds it is
+// issue: of some 390 instructions a sample of 64 lanes, 128 round and rectify
+// the two hidden layers and 56 are matrix products.
+// Three wavefronts per SIMD: asked for, since the compiler otherwise keeps 64 of
+// the registers in the accumulator file, for two wavefronts and 144 moves a
+// sample.  2,097,152 queries of a 1024^2 lattice, one B-spline sample each, GGX:
+// 52.6 -> 44 us; 5,000 queries 9.7 -> 8.0; 500,000 queries of 4 samples 41.3 ->
+// 34.3; every tap, 200,000 queries, 64.4 -> 57.3.  (Two wavefronts: 50.9, 7.5,
+// 43.0, 66.5; loads without a branch on the K block, so that the wait for one
+// sample's latents is not for the next one's too: 42.8, 7.8, 34.2, 56.9, but E4M3
+// latents 45.7 -> 46.8 and unshaded queries 44.9 -> 50.0.)
+template <int F_, int SHADE, int MODE, int FMT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_neural2d(NeuralCall c)
+{
+    constexpr int C = 8, O = 4;
+    MlpFrags<C, O> Fr;
     const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < c.n; base += stride)
-        neural2d_query<F_, SHADE, MODE, FMT>(c, Fr, base + threadIdx.x);
+    int64_t base = (int64_t)blockIdx.x * 256;
+    if constexpr (MODE != STOCH) {
+        load_frags<C, O>(static_cast<const uint16_t *>(c.mlp.params), Fr);
+        for (; base < c.n; base += stride)
+            neural2d_query<F_, SHADE, MODE, FMT>(c, Fr, base + threadIdx.x);
+    } else {
+        float2 coord = query_at(c, base + threadIdx.x), ahead = query_at(c, base + stride + threadIdx.x);
+        load_frags<C, O>(static_cast<const uint16_t *>(c.mlp.params), Fr);
+        // sample s of the query at q: its lattice point, and its latents on their way
+        const auto issue = [&](const Query2 &Q, int64_t q, int s, Latents2<FMT> &L) {
+            const uint4 w = pcg4d(make_uint4((uint32_t)q, (uint32_t)s, 0u, c.seed));
+            const int x = wrap_near(Q.ix + pick_off_2p24<F_>(Q.tx, u24i(w.x)), c.lat.res[0]);
+            const int y = wrap_near(Q.iy + pick_off_2p24<F_>(Q.ty, u24i(w.y)), c.lat.res[1]);
+            if (c.taps && Q.active) {
+                c.taps[(q * c.spp + s) * 2] = Q.ok ? x : SF_TAP_NONE;
+                c.taps[(q * c.spp + s) * 2 + 1] = Q.ok ? y : SF_TAP_NONE;
+            }
+            issue_latents2<C, FMT>(c.lat, (int64_t)y * c.lat.res[0] + x, c.lat.block_at(x, y, 0), L);
+        };
+        Query2 Q = place_query(c, base + threadIdx.x, coord);
+        Latents2<FMT> A, B;
+        issue(Q, base + threadIdx.x, 0, A);
+        int s = 0;
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        // one sample: the next one's latents are issued, then this one's decoded;
+        // false after the last
+        const auto sample = [&](const Latents2<FMT> &cur, Latents2<FMT> &nxt) -> bool {
+            const int64_t q = base + threadIdx.x;
+            const bool active = Q.active, ok = Q.ok, last = s + 1 == c.spp;
+            s = last ? 0 : s + 1;
+            if (last) {
+                base += stride;
+                coord = ahead;
+                ahead = query_at(c, base + stride + threadIdx.x);
+                Q = place_query(c, base + threadIdx.x, coord);
+            }
+            const bool more = base < c.n;
+            if (more)
+                issue(Q, base + threadIdx.x, s, nxt);
+            float y[O];
+            decode_latents2<C, O, FMT>(Fr, cur, y);
+            const float4 d = make_float4(__builtin_fminf(__builtin_fmaxf(y[0], 0.f), 1.f),
+                                         __builtin_fminf(__builtin_fmaxf(y[1], 0.f), 1.f),
+                                         __builtin_fminf(__builtin_fmaxf(y[2], 0.f), 1.f),
+                                         __builtin_fminf(__builtin_fmaxf(y[3], 0.f), 1.f));
+            const float4 v = shade<SHADE>(c.g, d);
+            acc[0] += v.x;
+            acc[1] += v.y;
+            acc[2] += v.z;
+            acc[3] += v.w;
+            if (last) {
+                const float inv = 1.0f / (float)c.spp;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    acc[k] = ok ? acc[k] * inv : __builtin_nanf("");
+                }
+                if (active)
+                    store<SHADE>(c.out, q, make_float4(acc[0], acc[1], acc[2], acc[3]));
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    acc[k] = 0.f;
+            }
+            return more;
+        };
+        while (sample(A, B) && sample(B, A))
+            ;
+    }
 }
 
 // Decoded outputs at given lattice points (no filtering, no clamping).
@@ -840,9 +1014,7 @@ __device__ __forceinline__ float decode_loaded(const MlpFrags<C, 1> &F, const St
         else
             zb = fp8x4_dequant(L.raw[G], __shfl(L.cs, 16 * G + (lane & 15)));
         const f32x4 d3 = mlp16<C, 1>(F, zb);
-        const float v = __shfl(d3[0], lane & 15);
-        if ((lane >> 4) == G)
-            y = v;
+        y = (lane >> 4) == G ? d3[0] : y;
     }
     return y;
 }

@@ -285,3 +285,41 @@ def test_ewa_pick_over_runs_of_rows(sf, orc, half, spp):
     ref, rt = orc.filter2d_aniso(ot, q, orc.EWA, orc.STOCHASTIC, spp=spp, seed=5, taps=True, amax=16)
     assert np.array_equal(taps.cpu().numpy(), rt)
     assert np.allclose(out.cpu().numpy(), ref, rtol=0, atol=1e-6)   # a mean of at most 5 exact texels
+
+
+# lattices whose taps wrap more than once, one lane, a full and a started
+# wavefront and workgroup, and more tiles than workgroups are resident
+@pytest.mark.parametrize("res", [(1, 1), (2, 1), (3, 2), (17, 5)])
+@pytest.mark.parametrize("n, spp", [(1, 1), (64, 2), (65, 3), (257, 1), (400000, 1), (270000, 2)])
+@pytest.mark.parametrize("fmt", [1, 2])
+def test_neural_texture_query_stream(sf, orc, res, n, spp, fmt):
+    """The picked lattice points are the oracle's for every query of the stream
+    compared, the values within BF16 rounding of the activations (2^-9 in each
+    of two hidden layers, some 1e-2 of the largest value)."""
+    _case("neural_stream", res, n, spp, fmt)
+    from paper_2407_06107_amd import inputs
+    C, O, H = 8, 4, 64
+    rng = np.random.default_rng(n + 10 * spp + res[0])
+    lat = rng.normal(size=(res[0] * res[1], C)).astype(np.float32)
+    grid = sf.sf_neural_quantize(torch.from_numpy(lat.ravel()).cuda(), 2, res, C, fmt, 2, (0, 0, 0), (1, 1, 1))
+    if fmt == sf.SF_LATENT_BF16:
+        Z = _bf16(lat)
+    else:
+        codes, scales = orc.quantize_fp8(lat.ravel(), 2, res, C, 2)
+        y, x = np.meshgrid(np.arange(res[1]), np.arange(res[0]), indexing="ij")
+        Z = orc.dequant_fp8(codes, scales[((y // 4) * -(-res[0] // 4) + x // 4).ravel()], C)
+    P = (0.25 * rng.normal(size=C * H + H + H * H + H + H * O + O)).astype(np.float32)
+    P[-O:] = 0.5
+    q = inputs.queries_uniform(n, seed=n)
+    q[n // 2, 1] = np.inf
+    q[n // 3, 0] = -1e-9
+    smp = sf.sampling(sf.SF_BSPLINE3, sf.SF_STOCHASTIC, spp, seed=9)
+    taps = torch.full((n, spp, 2), 99, dtype=torch.int32, device="cuda")
+    out = sf.sf_neural_decode(grid, sf.MLP(torch.from_numpy(P).cuda(), C, O), torch.from_numpy(q).cuda(), smp,
+                              dbg_taps=taps).cpu().numpy()
+    sub = np.unique(np.concatenate([np.arange(min(n, 200)), np.arange(max(0, n - 200), n), [n // 2, n // 3],
+                                    rng.integers(0, n, 400)]))
+    ref, rt = orc.neural_filter2d(res, C, H, O, Z, _bf16(P), q, orc.BSPLINE3, orc.STOCHASTIC, spp=spp, seed=9,
+                                  taps=True, subset=sub)
+    assert np.array_equal(taps.cpu().numpy()[sub], rt)
+    assert np.allclose(out[sub], ref, rtol=0, atol=2e-2, equal_nan=True)
