@@ -323,3 +323,37 @@ def test_neural_texture_query_stream(sf, orc, res, n, spp, fmt):
                                   taps=True, subset=sub)
     assert np.array_equal(taps.cpu().numpy()[sub], rt)
     assert np.allclose(out[sub], ref, rtol=0, atol=2e-2, equal_nan=True)
+
+
+@pytest.mark.parametrize("fmt", ["rgba8", "rgba32f", "dct"])
+@pytest.mark.parametrize("filt", ["NEAREST", "LINEAR", "BSPLINE3", "EWA"])
+def test_footprints_over_every_texture_format(sf, orc, fmt, filt):
+    """Each form of a footprint query, for each texture format, on a pyramid
+    whose sides are no multiples of a block: the taps are the oracle's, the values
+    within binary32 rounding of sums of at most 2048 terms of at most 1.6
+    (1e-5 of that)."""
+    _case("footprint_formats", fmt, filt)
+    rng = np.random.default_rng(17)
+    lv = _pyramid(67, 45, 23)
+    if fmt == "rgba32f":
+        lv = [rng.uniform(0, 1, x.shape).astype(np.float32) for x in lv]
+    if fmt == "dct":
+        ot, gt = orc.Tex2D.dct(lv, mip=orc.MIP_LINEAR), sf.Texture2D.dct(sf.Texture2D(lv, mip=sf.SF_MIP_LINEAR))
+    else:
+        ot, gt = _filter_case(orc, sf, lv, "REPEAT", True)
+    n = 700
+    q = rng.uniform(-0.1, 0.1, (n, 6)).astype(np.float32)
+    q[:, :2] = rng.uniform(-1.2, 1.7, (n, 2))
+    q[n // 2:, 2:] *= 0.2
+    for mode, gmode, spp in ((orc.STOCHASTIC, sf.SF_STOCHASTIC, 3), (orc.BEFORE, sf.SF_BEFORE, 1),
+                             (orc.AFTER, sf.SF_AFTER_EXACT, 1)):
+        smp = sf.sampling(getattr(sf, "SF_" + filt), gmode, spp, seed=3)
+        taps = torch.full((n, spp, 3), 99, dtype=torch.int32, device="cuda") if mode == orc.STOCHASTIC else None
+        out = sf.sf_filter2d_aniso(gt, torch.from_numpy(q).cuda(), smp, aniso_max=16, shade=1, ggx_params=sf.ggx(),
+                                   dbg_taps=taps).cpu().numpy()
+        ref = orc.filter2d_aniso(ot, q, getattr(orc, filt), mode, spp=spp, seed=3, shade=1, taps=taps is not None,
+                                 amax=16)
+        if taps is not None:
+            ref, rt = ref
+            assert np.array_equal(taps.cpu().numpy(), rt)
+        assert np.allclose(out, ref, rtol=1e-5, atol=1.6e-5), mode
