@@ -357,3 +357,31 @@ def test_footprints_over_every_texture_format(sf, orc, fmt, filt):
             ref, rt = ref
             assert np.array_equal(taps.cpu().numpy(), rt)
         assert np.allclose(out, ref, rtol=1e-5, atol=1.6e-5), mode
+
+
+@pytest.mark.parametrize("fmt", ["rgba8", "rgba32f", "dct"])
+@pytest.mark.parametrize("filt", ["NEAREST", "LINEAR", "BSPLINE3"])
+@pytest.mark.parametrize("plane_mode", [0, 1])
+def test_triplanar_over_every_texture_format(sf, orc, fmt, filt, plane_mode):
+    """Each form of a triplanar query, for each texture format, on a pyramid
+    whose sides are no multiples of a block, within binary32 rounding of sums of
+    at most 96 terms of at most 1.6."""
+    _case("triplanar_formats", fmt, filt, plane_mode)
+    rng = np.random.default_rng(18)
+    lv = _pyramid(67, 45, 29)
+    if fmt == "rgba32f":
+        lv = [rng.uniform(0, 1, x.shape).astype(np.float32) for x in lv]
+    if fmt == "dct":
+        ot, gt = orc.Tex2D.dct(lv, mip=orc.MIP_LINEAR), sf.Texture2D.dct(sf.Texture2D(lv, mip=sf.SF_MIP_LINEAR))
+    else:
+        ot, gt = _filter_case(orc, sf, lv, "REPEAT", True)
+    n = 500
+    q = rng.normal(size=(n, 8)).astype(np.float32)
+    q[:, 3:6] /= np.linalg.norm(q[:, 3:6], axis=1, keepdims=True)
+    q[:, 6] = rng.uniform(-0.5, 6.5, n)
+    for mode, gmode, spp in ((orc.STOCHASTIC, sf.SF_STOCHASTIC, 3), (orc.BEFORE, sf.SF_BEFORE, 1),
+                             (orc.AFTER, sf.SF_AFTER_EXACT, 1)):
+        smp = sf.sampling(getattr(sf, "SF_" + filt), gmode, spp, seed=3)
+        out = sf.sf_triplanar(gt, torch.from_numpy(q).cuda(), smp, 1.3, plane_mode, 1, sf.ggx()).cpu().numpy()
+        ref = orc.triplanar(ot, q, 1.3, plane_mode, getattr(orc, filt), mode, spp=spp, seed=3, shade=1)
+        assert np.allclose(out, ref, rtol=1e-5, atol=1.6e-5), mode
