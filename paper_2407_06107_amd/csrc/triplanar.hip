@@ -21,22 +21,11 @@ __device__ __forceinline__ void tri_uv(const float *p, int plane, float scale, f
     v = b * scale;
 }
 
-// Texel of a texture whose format the kernel knows, so that the loads of a
-// level's taps are in flight together, or (ANY_FORMAT) asks at each texel.
-// RGBA8, 1920 x 1080 pixels of a sphere: three planes, tent before shading 35 ->
-// 28.5 us, B-spline 121 -> 81; one plane 21.6 -> 16.2; one texel 17 -> 12-14.
-// DCT blocks: tent 83 us asking, 80 knowing; B-spline 286 and 315 (186
-// registers), so it asks; one texel 12.3 and 12.4, so it asks too.
-constexpr int ANY_FORMAT = -1;
-
-template <int FMT>
-__device__ __forceinline__ float4 texel_of(const Tex2DArgs &tx, int l, int wl, int x, int y)
-{
-    if constexpr (FMT == ANY_FORMAT)
-        return texel(tx, l, x, y);
-    else
-        return texel_at<FMT>(tx, tx.base + tx.off[l], l, wl, x, y);
-}
+// Which kernels know the format (texel_of).  RGBA8, 1920 x 1080 pixels of a
+// sphere: three planes, tent before shading 35 -> 28.5 us, B-spline 121 -> 81; one
+// plane 21.6 -> 16.2; one texel 17 -> 12-14.  DCT blocks: tent 83 us asking at
+// each texel, 80 knowing; B-spline 286 and 315 (186 registers), so it asks; one
+// texel 12.3 and 12.4, so it asks too.
 
 // One texel per sample on one plane: level pick (u_l), raster, per-axis
 // inverse-CDF picks on the 24-bit lattice indices ix_u, iy_u of the x and y
