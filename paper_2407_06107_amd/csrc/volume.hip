@@ -510,8 +510,9 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
 // weights, which sum to 1 +- 3e-7, into every one of 256 factors).  Both
 // modes then stay within about 20 u tau of the exact transmittance,
 // tau = -ln T, u = 2^-24.
-// Where a row's dt sigma_i all lie in [0, 1/16) (and dt >= 2^-24, so that no
-// power of it underflows), 1 - e^{-x} is x times a cubic fitted to
+// Where a row's dt sigma_i all lie in [0, 1/16) (and 2^-24 <= dt <= 2^24, so
+// that no power of it leaves binary32's range: with dt^4 infinite a zero tap
+// would give NaN), 1 - e^{-x} is x times a cubic fitted to
 // (1 - e^{-x})/x over that range (within 1.5e-9 of it, binary32 coefficients
 // included), and no exponential is taken; where all of a step's do, f_k > 1/2
 // and only a_k is formed.  Which form a row takes depends on its own taps
@@ -539,7 +540,7 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, uint32_t log_ru
     Tp.init();
     const float dt2 = dt * dt;
     const float c2 = dt2 * -0x1.ffffe8p-2f, c3 = (dt2 * dt) * 0x1.5542bcp-3f, c4 = (dt2 * dt2) * -0x1.4d42c4p-5f;
-    const float small = dt >= 0x1p-24f ? 0.0625f : 0.0f;
+    const float small = dt >= 0x1p-24f && dt <= 0x1p24f ? 0.0625f : 0.0f;
     march_taps<F, HALF, OCC>(c.vol, g, st == 0, r.k0, r.k1, stage[r.wave],
                              [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
         float acc = 0.0f;

@@ -385,3 +385,30 @@ def test_triplanar_over_every_texture_format(sf, orc, fmt, filt, plane_mode):
         out = sf.sf_triplanar(gt, torch.from_numpy(q).cuda(), smp, 1.3, plane_mode, 1, sf.ggx()).cpu().numpy()
         ref = orc.triplanar(ot, q, 1.3, plane_mode, getattr(orc, filt), mode, spp=spp, seed=3, shade=1)
         assert np.allclose(out, ref, rtol=1e-5, atol=1.6e-5), mode
+
+
+# steps below, just above and far above the world lengths (2^-24 to 2^24) for
+# which exact after takes its polynomial form: dt^4 overflows binary32 from
+# sides of some 2e11 at 40 steps, dt^3 from some 3e14
+@pytest.mark.parametrize("side", [1e-6, 1e9, 1e13, 1e17])
+@pytest.mark.parametrize("amp", [0.0, 1.0, 60.0])
+def test_every_tap_march_in_any_world_unit(sf, orc, cloud48, side, amp):
+    """Both every-tap modes against the oracle in volumes of any size, the
+    densities scaled to match, empty voxels among them (and an empty grid);
+    the brick mask changes no bit."""
+    from paper_2407_06107_amd import inputs
+    _case("world_unit", side, amp)
+    data = np.ascontiguousarray((cloud48[:40, :36, :44].astype(np.float32) * (amp / side)).astype(np.float32))
+    og, vol = _grids(orc, sf, data, side=side)
+    _, volm = _grids(orc, sf, data, side=side, brick=2)
+    for rays in (inputs.ortho_rays(20, 16, side=1.0, seed=3), inputs.random_rays(700, 1.0, seed=4)):
+        rays = rays.copy()
+        rays[:, [0, 1, 2, 6, 7]] *= np.float32(side)
+        rd = torch.from_numpy(rays).cuda()
+        for filt in ("NEAREST", "LINEAR", "BSPLINE3"):
+            for mode, gmode in ((orc.BEFORE, sf.SF_BEFORE), (orc.AFTER, sf.SF_AFTER_EXACT)):
+                ref = orc.raymarch(og, rays, 40, getattr(orc, filt), mode)
+                smp = sf.sampling(getattr(sf, "SF_" + filt), gmode)
+                T = sf.sf_raymarch(vol, rd, 40, smp).cpu().numpy()
+                assert np.allclose(T, ref, rtol=1e-5, atol=1e-7), (filt, gmode, np.nanmax(np.abs(T - ref)))
+                assert np.array_equal(T, sf.sf_raymarch(volm, rd, 40, smp).cpu().numpy()), (filt, gmode)
