@@ -678,13 +678,13 @@ __device__ __forceinline__ PerpFrame perp_frame(const float *r8, const float *sc
 
 // The samples of a ray are spread over G = 2^log_g adjacent lanes (a
 // power of two up to 64, inside one wave) and its steps over 2^log_split
-// wavefronts; their sums meet in a butterfly and in LDS, so small images
-// still fill the chip.
+// wavefronts; the steps' sums meet in LDS and the samples' in a butterfly, so
+// small images still fill the chip.
 template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2, bool JIT = false>
 __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCall c, uint32_t log_run,
                                                                      uint32_t log_split, int log_g)
 {
-    __shared__ float part[MAX_SPLIT_WAVES][64][3];
+    __shared__ float2 part[MAX_SPLIT_WAVES][64];
     const RaySegment rg(log_run, log_split, c.steps);
     const int G = 1 << log_g;
     const int64_t i = rg.i >> log_g;
@@ -759,29 +759,28 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
         acc[1].add(B[1]);
         acc[2].add(B[2]);
     }
+    if (log_split) {
+        // the segments' sums meet in segment order, as pairs, a band at a time
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            if (b)
+                __syncthreads();   // the band before is read
+            part[rg.wave][rg.lane] = make_float2(acc[b].s, acc[b].c);
+            __syncthreads();
+            if (rg.seg == 0)
+                for (int q = 1; q < (1 << log_split); ++q) {
+                    const float2 t = part[rg.wave + q][rg.lane];
+                    acc[b].add(t.x);
+                    acc[b].c += t.y;
+                }
+        }
+    }
     // the lanes' sums (at most 64, positive) meet in a butterfly
     float e[3] = {acc[0].value(), acc[1].value(), acc[2].value()};
     for (int m = G >> 1; m >= 1; m >>= 1) {
         e[0] += __shfl_xor(e[0], m);
         e[1] += __shfl_xor(e[1], m);
         e[2] += __shfl_xor(e[2], m);
-    }
-    if (log_split) {
-        // and the segments' in segment order
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-            part[rg.wave][rg.lane][b] = e[b];
-        __syncthreads();
-        if (rg.seg == 0) {
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                CompSum t;
-                t.init();
-                for (int q = 0; q < (1 << log_split); ++q)
-                    t.add(part[rg.wave + q][rg.lane][b]);
-                e[b] = t.value();
-            }
-        }
     }
     if (st == 3 || rg.seg != 0)
         return;

@@ -412,3 +412,40 @@ def test_every_tap_march_in_any_world_unit(sf, orc, cloud48, side, amp):
                 T = sf.sf_raymarch(vol, rd, 40, smp).cpu().numpy()
                 assert np.allclose(T, ref, rtol=1e-5, atol=1e-7), (filt, gmode, np.nanmax(np.abs(T - ref)))
                 assert np.array_equal(T, sf.sf_raymarch(volm, rd, 40, smp).cpu().numpy()), (filt, gmode)
+
+
+@pytest.mark.parametrize("spp", [1, 2, 16])
+def test_emission_sum_is_one_compensated_sum(sf, cloud48, spp):
+    """However a ray's steps are split over wavefronts, its radiance is the sum
+    of all its steps to within one rounding, 2^-24, and one more for each time
+    that lanes with samples of their own are added; the second order adds
+    terms x 2^-24 of it, at most 2^-12 (2^-10 allowed)."""
+    _case("emission_sum", spp)
+    grid = cloud48.astype(np.float32)
+    grid = np.where(grid > 0, 800 + 5200 * np.sqrt(grid / grid.max()), 0).astype(np.float32)
+    vol = sf.Volume(torch.from_numpy(grid).cuda(), side=1.0)
+    # a step is 2^-8 and spp a power of two, so that scaling the sum is exact
+    rng, steps = np.random.default_rng(2), 250
+    rays = np.zeros((3000, 8), np.float32)
+    rays[:, :3] = rng.random((3000, 3))
+    d = rng.normal(size=(3000, 3))
+    rays[:, 3:6] = d / np.linalg.norm(d, axis=1, keepdims=True)
+    rays[:, 7] = steps * 2.0**-8
+    smp = sf.sampling(sf.SF_BSPLINE3, sf.SF_STOCHASTIC, spp, seed=9)
+    taps = torch.empty((len(rays), spp, steps, 3), dtype=torch.int32, device="cuda")
+    L = sf.sf_raymarch_emission(vol, torch.from_numpy(rays).cuda(), steps, smp, dbg_taps=taps).cpu().numpy()
+    # the emission of each voxel, the same binary32 numbers as the march's
+    n = grid.shape[0]
+    z, y, x = np.meshgrid(*[np.arange(n)] * 3, indexing="ij")
+    pos = ((np.stack([x, y, z], -1).reshape(-1, 3) + 0.5) / n).astype(np.float32)
+    B = sf.sf_filter3d(vol, torch.from_numpy(pos).cuda(), sf.sampling(sf.SF_NEAREST, sf.SF_BEFORE),
+                       sf.SF_SHADE_PLANCK).cpu().numpy().astype(np.float64).reshape(n, n, n, 3)
+    t = taps.cpu().numpy().reshape(len(rays), -1, 3)
+    inside = ((t >= 0) & (t < n)).all(-1)
+    c = np.clip(t, 0, n - 1)
+    ref = np.where(inside[..., None], B[c[..., 2], c[..., 1], c[..., 0]], 0.0).sum(1) * 2.0**-8 / spp
+    lit = ref > 0
+    assert lit.mean() > 0.3
+    err = np.abs(L - ref)[lit] / ref[lit]
+    roundings = 1 + int(np.log2(spp))
+    assert err.max() <= roundings * 2.0**-24 * (1 + 2.0**-10), err.max() * 2.0**24
