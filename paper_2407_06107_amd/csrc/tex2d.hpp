@@ -184,7 +184,7 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(
 
 // Weighted sums of taps.  What is summed is linear in the weights, so that
 // as little as possible is done per tap and the rest once per sum:
-//   TAP_TEXEL   the texel's four channels (RGBA8: bytes, see tap_scale);
+//   TAP_TEXEL   the texel's four channels (RGBA8: bytes, see sum_scaled);
 //   TAP_GGX     its albedo channels (likewise) and its specular term, the only
 //               part of the GGX + Lambert model that is not linear in the texel;
 //   TAP_SHADED  the texel shaded as a whole (normal maps).
@@ -320,15 +320,22 @@ __device__ __forceinline__ float4 level_sum(const Tex2DArgs &tx, const GgxConst 
     return sum;
 }
 
-// A sum of taps as texel values (or radiance, once finished by sum_radiance):
+// x / 255 within half an ulp (and a little): the product with the reciprocal,
+// whose own rounding would bias every value by 2^-24, and the remainder's.
+__device__ __forceinline__ float over255(float x)
+{
+    const float k = 1.0f / 255.0f, q = x * k;
+    return __builtin_fmaf(__builtin_fmaf(-255.0f, q, x), k, q);
+}
+
+// A sum of taps as texel values (or radiance, once finished by sum_value):
 // RGBA8 sums hold bytes.
 template <int KIND, int FMT>
 __device__ __forceinline__ float4 sum_scaled(float4 s)
 {
     if constexpr (FMT != SF_RGBA8_UNORM || KIND == TAP_SHADED)
         return s;
-    const float k = 1.0f / 255.0f;
-    return make_float4(s.x * k, s.y * k, s.z * k, KIND == TAP_TEXEL ? s.w * k : s.w);
+    return make_float4(over255(s.x), over255(s.y), over255(s.z), KIND == TAP_TEXEL ? over255(s.w) : s.w);
 }
 
 // The lookup's value from its sum over all taps and levels.

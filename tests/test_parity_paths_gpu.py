@@ -449,3 +449,20 @@ def test_emission_sum_is_one_compensated_sum(sf, cloud48, spp):
     err = np.abs(L - ref)[lit] / ref[lit]
     roundings = 1 + int(np.log2(spp))
     assert err.max() <= roundings * 2.0**-24 * (1 + 2.0**-10), err.max() * 2.0**24
+
+
+@pytest.mark.parametrize("mode", ["BEFORE", "SPLIT"])
+@pytest.mark.parametrize("wrap", ["REPEAT", "CLAMP"])
+def test_byte_texels_are_divided_by_255(sf, orc, mode, wrap):
+    """A filtered RGBA8 value carries no bias from the scaling of its bytes:
+    the roundings of one lookup average out over the queries (some 1e-9), a
+    factor of binary32's nearest to 1/255 would stay (2^-24 of the value).
+    2^-27 allowed."""
+    from paper_2407_06107_amd import inputs
+    _case("byte_scale", mode, wrap)
+    lv = [np.random.default_rng(6).integers(120, 184, (64, 64, 4), dtype=np.uint8)]
+    ot, gt = _filter_case(orc, sf, lv, wrap, False)
+    q = inputs.queries_uniform(40000, seed=3)
+    ref = orc.filter2d(ot, q, orc.LINEAR, getattr(orc, mode), spp=1, seed=5)
+    out = sf.sf_filter2d(gt, torch.from_numpy(q).cuda(), sf.sampling(sf.SF_LINEAR, getattr(sf, "SF_" + mode), 1, seed=5))
+    assert abs((out.cpu().numpy() / ref - 1).mean()) <= 2.0**-27
