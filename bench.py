@@ -301,7 +301,7 @@ def gather_twin(torch, vol_occ, grid, rays_d, T):
 
 # The timed kernel: stochastic cubic B-spline, binary16 grid, independent
 # uniforms, no tap dump, occupancy mask, power-of-two addressing.
-TIMED_KERNEL = "_ZN3sfk11k_ray_stochILi2ELb1ELi0ELb0ELb1ELb1EEEvNS_12RaymarchCallEjj"
+TIMED_KERNEL = "_ZN3sfk11k_ray_stochILi2ELb1ELi0ELb0ELb1ELb1EEEvNS_12RaymarchCallENS_9SplitArgsE"
 
 
 def kernel_code_digest(lib_path=None, name=TIMED_KERNEL):

@@ -81,37 +81,73 @@ __device__ __forceinline__ void planck3(float T, float B[3])
 
 // ---------------------------------------------------------------- ray march
 // A ray's steps are split over 2^log_split wavefronts of a workgroup (1 for
-// launches with rays enough): wavefront w of a workgroup takes segment
-// w mod 2^log_split of 64 rays, and their sums meet in LDS in segment order.
-// Few rays then still fill the chip, and a launch of many ends with shorter
-// wavefronts (SplitGrid).
-struct RaySegment {
-    int64_t i;      // ray
-    int wave, lane, seg, k0, k1;
-    __device__ __forceinline__ RaySegment(uint32_t log_run, uint32_t log_split, int steps)
+// launches with rays enough): 64 rays have as many neighbouring wavefronts, which
+// take their steps (or blocks of steps) in turn, and whose sums meet in LDS in
+// wavefront order.  Few rays then still fill the chip, and a launch of many ends
+// with shorter wavefronts (SplitGrid).  In turn, not a stretch of the ray each:
+// the rays on their way stay at one depth together and find their voxels in the
+// caches.  Rays that lie apart share no lines, and more of them on their way at
+// once find fewer: those are split over 2^log_apart wavefronts only, and the
+// group's others have no steps.  65,536 rays x 256 steps, trilinear stochastic, 256^3
+// binary16 cloud: 64 x 64 pixels of 16 rays 97 us unsplit, 57 in 16 stretches and 38
+// in turns of four; random rays 159, 242 and 160 us.
+struct SplitArgs {
+    uint32_t log_run, log_split, log_apart;
+};
+
+struct RaySplit {
+    int64_t i;         // ray
+    int wave, lane;
+    int part, parts;   // the wavefront's place among those of its rays
+    int first, stride; // its steps (or blocks): first, first + stride, ..
+    __device__ __forceinline__ RaySplit(const SplitArgs &sp)
     {
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         lane = threadIdx.x & 63;
-        seg = wave & ((1 << log_split) - 1);
-        i = (int64_t)xcd_block(blockIdx.x, log_run) * (blockDim.x >> log_split) + (((wave >> log_split) << 6) | lane);
-        k0 = (int)(((int64_t)steps * seg) >> log_split);
-        k1 = (int)(((int64_t)steps * (seg + 1)) >> log_split);
+        parts = 1 << sp.log_split;
+        part = wave & (parts - 1);
+        first = part;
+        stride = parts;
+        i = (int64_t)xcd_block(blockIdx.x, sp.log_run) * (blockDim.x >> sp.log_split) +
+            (((wave >> sp.log_split) << 6) | lane);
+    }
+    __device__ __forceinline__ void share(const SplitArgs &sp, bool together, int steps)
+    {
+        stride = 1 << (together ? sp.log_split : sp.log_apart);
+        first = part < stride ? part : steps;
     }
 };
+
+// Whether the wavefront's rays lie together: of the lanes that march beside
+// one that does, three in four are within 16 voxels of it half-way.  All lanes
+// call it; the wavefronts of the same rays find the same.
+__device__ __forceinline__ bool rays_together(const RayGeom &g, bool march, int steps)
+{
+    float p[3];
+    int i0[3];
+    step_pos(g, 0.5f * (float)steps, p, i0);
+    const bool pair = march & (__builtin_amdgcn_update_dpp(0, (int)march, 0x111, 0xf, 0xf, false) != 0);   // row_shr:1
+    bool near = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        near &= (uint32_t)(i0[a] - __builtin_amdgcn_update_dpp(0, i0[a], 0x111, 0xf, 0xf, false) + 16) <= 32u;
+    return 4 * __popcll(__ballot(pair & near)) >= 3 * __popcll(__ballot(pair));
+}
 
 constexpr int MAX_SPLIT_WAVES = 16;
 
 template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
-__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall c, uint32_t log_run, uint32_t log_split)
+__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall c, SplitArgs sp)
 {
     static_assert(!(DBG && OCC), "the tap dump records every step, so it never skips bricks");
     __shared__ float2 part[MAX_SPLIT_WAVES][64];
-    const RaySegment r(log_run, log_split, c.steps);
+    RaySplit r(sp);
     const int64_t i = r.i;
     RayGeom g = {};
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
+    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     // optical depth and the mean over samples as compensated binary32 sums:
@@ -131,9 +167,10 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
             // software pipeline: a step's voxel is added one step later, so its
             // load overlaps the next step's arithmetic
             uint32_t pend = 0;
-            float kh = (float)r.k0 + 0.5f;
+            float kh = (float)r.first + 0.5f;
+            const float dk = (float)r.stride;
             if constexpr (OCC) {
-                // With the brick mask, the brick word of step k + 1 is loaded
+                // With the brick mask, the brick word of the next step is loaded
                 // during step k as well, ahead of step k's voxel, and every step
                 // loads a voxel (a step in an empty brick loads past the grid's
                 // end and adds the 0.0 it reads, which leaves the compensated
@@ -149,7 +186,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
                 };
                 auto step = [&](int k, const At &cur, At &nxt) {
                     const bool empty = __builtin_amdgcn_ubfe(cur.word, cur.bit, 1u) != 0u;
-                    kh += 1.0f;
+                    kh += dk;
                     step_pos(g, kh, nxt.p, nxt.i0);
                     nxt.word = brick_word(rm, c.vol, nxt.i0, nxt.bit);
                     tau.add(bits_value<HALF>(pend));   // step k - 1
@@ -171,16 +208,16 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
                 // depends on the brick index so that it is not moved ahead)
                 __builtin_amdgcn_sched_barrier(0);
                 pend = voxel_bits<HALF>(rs, kOut | (a.bit >> 31));
-                int k = r.k0;
-                for (; k + 1 < r.k1; k += 2) {
+                int k = r.first;
+                for (; k + r.stride < c.steps; k += 2 * r.stride) {
                     step(k, a, b);
-                    step(k + 1, b, a);
+                    step(k + r.stride, b, a);
                 }
-                if (k < r.k1)
+                if (k < c.steps)
                     step(k, a, b);
                 tau.add(bits_value<HALF>(pend));
             } else {
-                for (int k = r.k0; k < r.k1; ++k, kh += 1.0f) {
+                for (int k = r.first; k < c.steps; k += r.stride, kh += dk) {
                     int i0[3], o[3];
                     float p[3], t[3];
                     step_pos(g, kh, p, i0);
@@ -200,12 +237,12 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
                 tau.add(bits_value<HALF>(pend));
             }
         }
-        if (log_split) {
-            // the segments' sums meet in segment order
+        if (sp.log_split) {
+            // the wavefronts' sums meet in order
             part[r.wave][r.lane] = make_float2(tau.s, tau.c);
             __syncthreads();
-            if (r.seg == 0)
-                for (int q = 1; q < (1 << log_split); ++q) {
+            if (r.part == 0)
+                for (int q = 1; q < r.parts; ++q) {
                     const float2 t = part[r.wave + q][r.lane];
                     tau.add(t.x);
                     tau.c += t.y;
@@ -214,7 +251,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
         }
         Tsum.add(expf(-(g.dt * tau.value())));
     }
-    if (r.seg != 0 || st == 3)
+    if (r.part != 0 || st == 3)
         return;
     if (st != 0) {
         c.T[i] = st == 1 ? 1.0f : __builtin_nanf("");
@@ -385,13 +422,13 @@ __device__ __forceinline__ uint32_t stage_box(const VolArgs &v, float *vox, cons
 }
 
 // The march over every tap: eval(wx, wy, wz, taps, largest) once for each
-// step of this lane that is not in a provably empty brick, in step order;
+// step of this lane and wavefront that is not in a provably empty brick, in step order;
 // `largest` bounds the step's taps from above if they are all non-negative,
 // and is infinite otherwise.  Called by all lanes of a wavefront;
 // `march` marks those with a ray.
 template <int F, bool HALF, bool OCC, typename Eval>
-__device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, bool march, int k0, int steps,
-                                           float *vox, Eval &&eval)
+__device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, bool march, int steps,
+                                           const RaySplit &r, float *vox, Eval &&eval)
 {
     constexpr int NT = Taps<F>::n;
     constexpr int first = Taps<F>::first, last = F == NEAREST ? 1 : Taps<F>::first + Taps<F>::n - 1;
@@ -402,101 +439,105 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
         rm = occ_rsrc(v);
     int mtry = STAGE_STEPS;   // steps of the next box
     int pause = 0;            // steps still to be read from the grid without trying
-    for (int k = k0; k < steps;) {
-        const int m = min(pause > 0 ? min(pause, STAGE_STEPS) : mtry, steps - k);
-        // brick bits of the m steps; a lane takes part while it has one to read
-        uint32_t full = 0;
-        if constexpr (OCC) {
-            if (march) {
+    // the wavefront's steps come in blocks of a box
+    for (int kb = STAGE_STEPS * r.first; kb < steps; kb += STAGE_STEPS * r.stride) {
+        const int k1 = min(kb + STAGE_STEPS, steps);
+        for (int k = kb; k < k1;) {
+            const int m = min(pause > 0 ? min(pause, STAGE_STEPS) : mtry, k1 - k);
+            // brick bits of the m steps; a lane takes part while it has one to read
+            uint32_t full = 0;
+            if constexpr (OCC) {
+                if (march) {
 #pragma unroll
-                for (int j = 0; j < STAGE_STEPS; ++j) {
-                    if (j < m) {
-                        float p[3];
-                        int i0[3];
-                        step_pos(g, (float)(k + j) + 0.5f, p, i0);
-                        full |= brick_empty_clamped(rm, v, i0) ? 0u : 1u << j;
+                    for (int j = 0; j < STAGE_STEPS; ++j) {
+                        if (j < m) {
+                            float p[3];
+                            int i0[3];
+                            step_pos(g, (float)(k + j) + 0.5f, p, i0);
+                            full |= brick_empty_clamped(rm, v, i0) ? 0u : 1u << j;
+                        }
                     }
                 }
+            } else {
+                full = march ? (1u << m) - 1u : 0u;
             }
-        } else {
-            full = march ? (1u << m) - 1u : 0u;
-        }
-        if (!__any(full != 0u)) {   // nothing to read in these steps
-            k += m;
-            mtry = STAGE_STEPS;
-            pause = 0;
-            continue;
-        }
-        StageBox b = {};
-        bool staged = false;
-        float largest = __builtin_inff();
-        if (pause > 0) {
-            pause -= m;
-        } else {
-            // the box of the wavefront's taps; a lane's cells lie between
-            // those of the first and the last step (positions are linear in k)
-            float p[3];
-            int ia[3], ib[3], lo[3], hi[3];
-            step_pos(g, (float)k + 0.5f, p, ia);
-            step_pos(g, (float)(k + m - 1) + 0.5f, p, ib);
+            if (!__any(full != 0u)) {   // nothing to read in these steps
+                k += m;
+                mtry = STAGE_STEPS;
+                pause = 0;
+                continue;
+            }
+            StageBox b = {};
+            bool staged = false;
+            float largest = __builtin_inff();
+            if (pause > 0) {
+                pause -= m;
+            } else {
+                // the box of the wavefront's taps; a lane's cells lie between
+                // those of the first and the last step (positions are linear in k)
+                float p[3];
+                int ia[3], ib[3], lo[3], hi[3];
+                step_pos(g, (float)k + 0.5f, p, ia);
+                step_pos(g, (float)(k + m - 1) + 0.5f, p, ib);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                lo[a] = wave_min(full ? min(ia[a], ib[a]) : 0x3fffffff);
-                hi[a] = wave_max(full ? max(ia[a], ib[a]) : -0x3fffffff);
+                for (int a = 0; a < 3; ++a) {
+                    lo[a] = wave_min(full ? min(ia[a], ib[a]) : 0x3fffffff);
+                    hi[a] = wave_max(full ? max(ia[a], ib[a]) : -0x3fffffff);
+                }
+                const int nx = hi[0] - lo[0] + 1 + last - first, ny = hi[1] - lo[1] + 1 + last - first,
+                          nz = hi[2] - lo[2] + 1 + last - first;
+                const int u = (nx + 3) >> 2;
+                const int plane = u <= STAGE_UNITS && ny <= STAGE_UNITS ? u * ny | 1 : STAGE_UNITS + 1;
+                // A trilinear step has 8 taps to read where a tricubic one has 64, so
+                // its box may hold no more units per step than four steps' share:
+                // 4096 rays a voxel apart, 64^3 grid, 256 steps, before: 251 us with
+                // a full box for a single step, 97 with this line, 191 with each ray
+                // reading its own taps from one wavefront (tricubic: 433 with a full
+                // box, 1764 without).
+                const int room = NT == 4 ? STAGE_UNITS : STAGE_UNITS / STAGE_STEPS * m;
+                const bool fits = plane <= STAGE_UNITS && nz <= STAGE_UNITS && plane * nz <= room;
+                if (!fits) {
+                    if (m > 1)
+                        mtry = m >> 1;
+                    else
+                        pause = STAGE_PAUSE;
+                    continue;
+                }
+                // as many steps as can be next time if twice the box would fit
+                mtry = 2 * plane * nz <= STAGE_UNITS ? STAGE_STEPS : m;
+                b.x0 = lo[0] + first, b.y0 = lo[1] + first, b.z0 = lo[2] + first;
+                b.nyb = ny, b.nzb = nz, b.u = u, b.plane = plane;
+                staged = true;
+                // Lanes read what others of the wavefront wrote: its LDS
+                // instructions run in order, the fences keep the compiler to it.
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t top = stage_box<HALF>(v, vox, b);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                largest = top < 0x7f800000u ? __uint_as_float(top) : __builtin_inff();
             }
-            const int nx = hi[0] - lo[0] + 1 + last - first, ny = hi[1] - lo[1] + 1 + last - first,
-                      nz = hi[2] - lo[2] + 1 + last - first;
-            const int u = (nx + 3) >> 2;
-            const int plane = u <= STAGE_UNITS && ny <= STAGE_UNITS ? u * ny | 1 : STAGE_UNITS + 1;
-            // A trilinear step has 8 taps to read where a tricubic one has 64, so
-            // its box may hold no more units per step than four steps' share:
-            // 4096 rays a voxel apart, 64^3 grid, 256 steps, before: 251 us with
-            // a full box for a single step, 97 with this line, 191 with each ray
-            // reading its own taps from one wavefront (tricubic: 433 with a full
-            // box, 1764 without).
-            const int room = NT == 4 ? STAGE_UNITS : STAGE_UNITS / STAGE_STEPS * m;
-            const bool fits = plane <= STAGE_UNITS && nz <= STAGE_UNITS && plane * nz <= room;
-            if (!fits) {
-                if (m > 1)
-                    mtry = m >> 1;
+            for (int j = 0; j < m; ++j) {
+                if (!((full >> j) & 1u))
+                    continue;
+                int i0[3];
+                float t[3], wx[4], wy[4], wz[4];
+                step_coords(g, (float)(k + j) + 0.5f, i0, t);
+                if constexpr (F == NEAREST) {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        i0[a] += t[a] >= 0.5f;
+                }
+                axis_weights<F>(t[0], wx);
+                axis_weights<F>(t[1], wy);
+                axis_weights<F>(t[2], wz);
+                if (staged)
+                    eval(wx, wy, wz, StageTaps<F>(vox, b, i0), largest);
                 else
-                    pause = STAGE_PAUSE;
-                continue;
+                    eval(wx, wy, wz, GridTaps<F, HALF>(v, rs, i0), largest);
             }
-            // as many steps as can be next time if twice the box would fit
-            mtry = 2 * plane * nz <= STAGE_UNITS ? STAGE_STEPS : m;
-            b.x0 = lo[0] + first, b.y0 = lo[1] + first, b.z0 = lo[2] + first;
-            b.nyb = ny, b.nzb = nz, b.u = u, b.plane = plane;
-            staged = true;
-            // Lanes read what others of the wavefront wrote: its LDS
-            // instructions run in order, the fences keep the compiler to it.
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t top = stage_box<HALF>(v, vox, b);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            largest = top < 0x7f800000u ? __uint_as_float(top) : __builtin_inff();
+            k += m;
         }
-        for (int j = 0; j < m; ++j) {
-            if (!((full >> j) & 1u))
-                continue;
-            int i0[3];
-            float t[3], wx[4], wy[4], wz[4];
-            step_coords(g, (float)(k + j) + 0.5f, i0, t);
-            if constexpr (F == NEAREST) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    i0[a] += t[a] >= 0.5f;
-            }
-            axis_weights<F>(t[0], wx);
-            axis_weights<F>(t[1], wy);
-            axis_weights<F>(t[2], wz);
-            if (staged)
-                eval(wx, wy, wz, StageTaps<F>(vox, b, i0), largest);
-            else
-                eval(wx, wy, wz, GridTaps<F, HALF>(v, rs, i0), largest);
-        }
-        k += m;
     }
 }
 
@@ -523,15 +564,16 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
 // modes are bound by vector instructions (about 570 and 320 per 64-ray step)
 // and the LDS reads of the rows together.
 template <int F, bool HALF, int MODE, bool OCC>
-__global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, uint32_t log_run, uint32_t log_split)
+__global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, SplitArgs sp)
 {
     __shared__ __attribute__((aligned(16))) float stage[4][4 * STAGE_UNITS];
-    const RaySegment r(log_run, log_split, c.steps);
+    RaySplit r(sp);
     const int64_t i = r.i;
     RayGeom g = {};
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
+    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
     constexpr int NT = Taps<F>::n;
     const float dt = g.dt;
     CompSum tau;
@@ -541,7 +583,7 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, uint32_t log_ru
     const float dt2 = dt * dt;
     const float c2 = dt2 * -0x1.ffffe8p-2f, c3 = (dt2 * dt) * 0x1.5542bcp-3f, c4 = (dt2 * dt2) * -0x1.4d42c4p-5f;
     const float small = dt >= 0x1p-24f && dt <= 0x1p24f ? 0.0625f : 0.0f;
-    march_taps<F, HALF, OCC>(c.vol, g, st == 0, r.k0, r.k1, stage[r.wave],
+    march_taps<F, HALF, OCC>(c.vol, g, st == 0, c.steps, r, stage[r.wave],
                              [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
         float acc = 0.0f;
         if constexpr (MODE == BEFORE) {
@@ -619,13 +661,13 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, uint32_t log_ru
                 Tp.mul_one_minus(acc);
         }
     });
-    if (log_split) {
-        // the segments' results meet in segment order
+    if (sp.log_split) {
+        // the wavefronts' results meet in order
         stage[r.wave][2 * r.lane] = MODE == BEFORE ? tau.s : Tp.hi;
         stage[r.wave][2 * r.lane + 1] = MODE == BEFORE ? tau.c : Tp.lo;
         __syncthreads();
-        if (r.seg == 0)
-            for (int q = 1; q < (1 << log_split); ++q) {
+        if (r.part == 0)
+            for (int q = 1; q < r.parts; ++q) {
                 const float a = stage[r.wave + q][2 * r.lane], b = stage[r.wave + q][2 * r.lane + 1];
                 if constexpr (MODE == BEFORE) {
                     tau.add(a);
@@ -635,7 +677,7 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, uint32_t log_ru
                 }
             }
     }
-    if (r.seg != 0 || st == 3)
+    if (r.part != 0 || st == 3)
         return;
     if (st != 0)
         c.T[i] = st == 1 ? 1.0f : __builtin_nanf("");
@@ -681,11 +723,10 @@ __device__ __forceinline__ PerpFrame perp_frame(const float *r8, const float *sc
 // wavefronts; the steps' sums meet in LDS and the samples' in a butterfly, so
 // small images still fill the chip.
 template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2, bool JIT = false>
-__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCall c, uint32_t log_run,
-                                                                     uint32_t log_split, int log_g)
+__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCall c, SplitArgs sp, int log_g)
 {
     __shared__ float2 part[MAX_SPLIT_WAVES][64];
-    const RaySegment rg(log_run, log_split, c.steps);
+    RaySplit rg(sp);
     const int G = 1 << log_g;
     const int64_t i = rg.i >> log_g;
     const int lane = rg.lane & (G - 1);
@@ -693,6 +734,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
     int st = 3;   // no ray (the whole group of lanes shares i)
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
+    rg.share(sp, rays_together(g, st == 0, c.steps), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     __amdgpu_buffer_rsrc_t rm;
@@ -712,8 +754,9 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
         if constexpr (JIT)
             hj.init((uint32_t)i, (uint32_t)s | 0x80000000u, c.seed);
         uint32_t pend = 0;
-        float kh = (float)rg.k0 + 0.5f;
-        for (int k = rg.k0; k < rg.k1; ++k, kh += 1.0f) {
+        float kh = (float)rg.first + 0.5f;
+        const float dk = (float)rg.stride;
+        for (int k = rg.first; k < c.steps; k += rg.stride, kh += dk) {
             int i0[3], o[3];
             float t[3];
             if constexpr (JIT) {
@@ -759,16 +802,16 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
         acc[1].add(B[1]);
         acc[2].add(B[2]);
     }
-    if (log_split) {
-        // the segments' sums meet in segment order, as pairs, a band at a time
+    if (sp.log_split) {
+        // the wavefronts' sums meet in order, as pairs, a band at a time
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             if (b)
                 __syncthreads();   // the band before is read
             part[rg.wave][rg.lane] = make_float2(acc[b].s, acc[b].c);
             __syncthreads();
-            if (rg.seg == 0)
-                for (int q = 1; q < (1 << log_split); ++q) {
+            if (rg.part == 0)
+                for (int q = 1; q < rg.parts; ++q) {
                     const float2 t = part[rg.wave + q][rg.lane];
                     acc[b].add(t.x);
                     acc[b].c += t.y;
@@ -782,7 +825,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
         e[1] += __shfl_xor(e[1], m);
         e[2] += __shfl_xor(e[2], m);
     }
-    if (st == 3 || rg.seg != 0)
+    if (st == 3 || rg.part != 0)
         return;
     if (st != 0) {
         const float v = st == 1 ? 0.0f : __builtin_nanf("");
@@ -813,21 +856,22 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
 // sum_i w_i B(T_i) after; binary32 weights and per-step sums of positive
 // terms, steps summed with compensation.
 template <int F, bool HALF, int MODE, bool OCC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_emit_det(RaymarchCall c, uint32_t log_run, uint32_t log_split)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_emit_det(RaymarchCall c, SplitArgs sp)
 {
     __shared__ __attribute__((aligned(16))) float stage[4][4 * STAGE_UNITS];
-    const RaySegment r(log_run, log_split, c.steps);
+    RaySplit r(sp);
     const int64_t i = r.i;
     RayGeom g = {};
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
+    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
     constexpr int NT = Taps<F>::n;
     CompSum acc[3];
     acc[0].init();
     acc[1].init();
     acc[2].init();
-    march_taps<F, HALF, OCC>(c.vol, g, st == 0, r.k0, r.k1, stage[r.wave],
+    march_taps<F, HALF, OCC>(c.vol, g, st == 0, c.steps, r, stage[r.wave],
                              [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
         float e[3] = {0.0f, 0.0f, 0.0f};
         // exact after: a plane at a time and its rows one by one, since all 64
@@ -876,23 +920,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             acc[2].add(e[2]);
         }
     });
-    if (log_split) {
-        // the segments' sums meet in segment order
+    if (sp.log_split) {
+        // the wavefronts' sums meet in order
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             stage[r.wave][6 * r.lane + 2 * b] = acc[b].s;
             stage[r.wave][6 * r.lane + 2 * b + 1] = acc[b].c;
         }
         __syncthreads();
-        if (r.seg == 0)
-            for (int q = 1; q < (1 << log_split); ++q)
+        if (r.part == 0)
+            for (int q = 1; q < r.parts; ++q)
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
                     acc[b].add(stage[r.wave + q][6 * r.lane + 2 * b]);
                     acc[b].c += stage[r.wave + q][6 * r.lane + 2 * b + 1];
                 }
     }
-    if (r.seg != 0 || st == 3)
+    if (r.part != 0 || st == 3)
         return;
 #pragma unroll
     for (int b = 0; b < 3; ++b)
@@ -1117,23 +1161,41 @@ hipError_t launch_build_occupancy(const VolArgs &v, uint32_t *occ, hipStream_t s
 static uint32_t blocks_for(int64_t n) { return (uint32_t)((n + 255) / 256); }
 
 // Launch shape of a march of n rays: workgroups of `lanes` lanes, each ray
-// over 2^log_split wavefronts, until there are 2 Mi lanes (four times what
-// the chip holds), 2^most wavefronts per ray or fewer than 16 steps in a
-// segment.  Measured (512^3 cloud, tricubic stochastic, 256 steps, without
-// and with the split): 1 Mi rays 500 and 485 us, 262,144 rays 230 and 180,
-// 65,536 rays of sparse pixels 137 and 90, 4096 rays 105 and 30.
+// over 2^log_split wavefronts, until there are `wanted` lanes, 2^most
+// wavefronts per ray or fewer than 16 steps each.  Stochastic marches (`once`)
+// read one voxel a step and want 2^18 lanes, half of what the chip holds, and
+// one split up to 2 Mi rays; marches over every tap want more, the more taps (a
+// staged box is a long wait).  Rays that lie apart (rays_together) are split
+// only up to `apart` lanes, while all wavefronts launched fit the chip at once
+// (past that, those without steps would keep others out).
+struct MarchLanes {
+    int64_t wanted, apart;
+    bool once;
+};
+constexpr MarchLanes STOCH_LANES = {1 << 18, 1 << 17, true};
+template <int F>
+constexpr MarchLanes DET_LANES = F == NEAREST   ? MarchLanes{1 << 19, 1 << 17, false}
+                                 : F == LINEAR ? MarchLanes{1 << 20, 1 << 16, false}
+                                               : MarchLanes{1 << 21, 1 << 18, false};
+
 struct SplitGrid {
-    uint32_t blocks, lanes, log_run, log_split;
-    SplitGrid(int64_t n, int steps, uint32_t most)
+    uint32_t blocks, lanes;
+    SplitArgs args;
+    SplitGrid(int64_t n, int steps, uint32_t most, const MarchLanes &m)
     {
-        log_split = 0;
-        while (log_split < most && (n << log_split) < (1 << 21) && (steps >> (log_split + 1)) >= 8)
+        uint32_t log_split = 0, log_apart = 0;
+        while (log_split < most && (steps >> (log_split + 1)) >= 8 &&
+               ((n << log_split) < m.wanted || (m.once && log_split == 0 && n < (1 << 21))))
             ++log_split;
+        while (log_apart < log_split && (n << (log_apart + 1)) <= m.apart)
+            ++log_apart;
+        if ((n << log_split) > (1 << 19))
+            log_apart = log_split;
         lanes = 64u << (log_split > 2 ? log_split : 2);
         const uint32_t rays = lanes >> log_split;
         const XcdGrid xg((uint32_t)((n + rays - 1) / rays), rays);
         blocks = xg.blocks;
-        log_run = xg.log_run;
+        args = {xg.log_run, log_split, log_apart};
     }
 };
 
@@ -1141,17 +1203,17 @@ template <int F, bool HALF, bool OCC, bool P2>
 static void launch_ray_fo(const RaymarchCall &c, hipStream_t s)
 {
     if (c.mode == STOCH) {
-        const SplitGrid sg(c.n, c.steps, 4);
+        const SplitGrid sg(c.n, c.steps, 4, STOCH_LANES);
         if (c.variant)
-            k_ray_stoch<F, HALF, 1, false, OCC, P2><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+            k_ray_stoch<F, HALF, 1, false, OCC, P2><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
         else
-            k_ray_stoch<F, HALF, 0, false, OCC, P2><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+            k_ray_stoch<F, HALF, 0, false, OCC, P2><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     } else if (c.mode == BEFORE) {
-        const SplitGrid sg(c.n, c.steps, 2);
-        k_ray_det<F, HALF, BEFORE, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+        const SplitGrid sg(c.n, c.steps, 2, DET_LANES<F>);
+        k_ray_det<F, HALF, BEFORE, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     } else {
-        const SplitGrid sg(c.n, c.steps, 2);
-        k_ray_det<F, HALF, AFTER, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+        const SplitGrid sg(c.n, c.steps, 2, DET_LANES<F>);
+        k_ray_det<F, HALF, AFTER, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     }
 }
 
@@ -1161,11 +1223,11 @@ static hipError_t launch_ray_f(const RaymarchCall &c, hipStream_t s)
     const bool p2 = c.vol.lx >= 0;
     if (c.mode == STOCH && c.taps) {
         // the tap dump records every step, so it never skips empty bricks
-        const SplitGrid sg(c.n, c.steps, 4);
+        const SplitGrid sg(c.n, c.steps, 4, STOCH_LANES);
         if (c.variant)
-            k_ray_stoch<F, HALF, 1, true, false, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+            k_ray_stoch<F, HALF, 1, true, false, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
         else
-            k_ray_stoch<F, HALF, 0, true, false, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+            k_ray_stoch<F, HALF, 0, true, false, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     } else if (c.vol.occ) {
         if (p2)
             launch_ray_fo<F, HALF, true, true>(c, s);
@@ -1184,12 +1246,12 @@ template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
 static void launch_emit_stoch(const RaymarchCall &c, hipStream_t s)
 {
     const int G = lane_group(c.n, c.spp);
-    const SplitGrid sg(c.n * G, c.steps, 4);
+    const SplitGrid sg(c.n * G, c.steps, 4, STOCH_LANES);
     const int lg = __builtin_ctz(G);
     if (c.footprint > 0.0f)
-        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split, lg);
+        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args, lg);
     else
-        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split, lg);
+        k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, false><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args, lg);
 }
 
 template <int F, bool HALF, bool OCC, bool P2>
@@ -1201,11 +1263,11 @@ static void launch_emit_fo(const RaymarchCall &c, hipStream_t s)
         else
             launch_emit_stoch<F, HALF, 0, false, OCC, P2>(c, s);
     } else if (c.mode == BEFORE) {
-        const SplitGrid sg(c.n, c.steps, 2);
-        k_emit_det<F, HALF, BEFORE, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+        const SplitGrid sg(c.n, c.steps, 2, DET_LANES<F>);
+        k_emit_det<F, HALF, BEFORE, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     } else {
-        const SplitGrid sg(c.n, c.steps, 2);
-        k_emit_det<F, HALF, AFTER, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.log_run, sg.log_split);
+        const SplitGrid sg(c.n, c.steps, 2, DET_LANES<F>);
+        k_emit_det<F, HALF, AFTER, OCC><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args);
     }
 }
 

@@ -466,3 +466,39 @@ def test_byte_texels_are_divided_by_255(sf, orc, mode, wrap):
     ref = orc.filter2d(ot, q, orc.LINEAR, getattr(orc, mode), spp=1, seed=5)
     out = sf.sf_filter2d(gt, torch.from_numpy(q).cuda(), sf.sampling(sf.SF_LINEAR, getattr(sf, "SF_" + mode), 1, seed=5))
     assert abs((out.cpu().numpy() / ref - 1).mean()) <= 2.0**-27
+
+
+# as many rays as are split over four wavefronts, or (apart) one: the shares of
+# steps of wavefronts whose rays lie together, lie apart, and of both in one launch
+@pytest.mark.parametrize("kind", ["together", "apart", "mixed"])
+@pytest.mark.parametrize("steps", [16, 41, 64])
+def test_march_shares_its_steps_among_wavefronts(sf, orc, cloud48, kind, steps):
+    """Every march of 65,537 rays against the oracle: all modes, the emission
+    too, with and without the brick mask."""
+    from paper_2407_06107_amd import inputs
+    _case("march_shares", kind, steps)
+    n = 65537
+    rays = inputs.random_rays(n, 1.0, seed=8)
+    if kind != "apart":
+        near = np.concatenate([inputs.ortho_rays(256, 1, side=1.0, seed=3), rays[:1]])
+        rays = near if kind == "together" else np.where((np.arange(n) // 64 % 2 == 0)[:, None], near, rays)
+    rays = np.ascontiguousarray(rays.astype(np.float32))
+    rd = torch.from_numpy(rays).cuda()
+    data = np.ascontiguousarray(cloud48[:40, :36, :44])
+    hot = data.astype(np.float32)
+    hot = np.where(hot > 0, 800 + 5200 * np.sqrt(hot / hot.max()), 0).astype(np.float16)
+    og, vol = _grids(orc, sf, data)
+    _, volm = _grids(orc, sf, data, brick=2)
+    ogh, volh = _grids(orc, sf, hot, brick=2)
+    for filt in ("NEAREST", "LINEAR", "BSPLINE3"):
+        for mode, gmode in ((orc.STOCHASTIC, sf.SF_STOCHASTIC), (orc.BEFORE, sf.SF_BEFORE), (orc.AFTER, sf.SF_AFTER_EXACT)):
+            smp = sf.sampling(getattr(sf, "SF_" + filt), gmode, 1, seed=3)
+            ref = orc.raymarch(og, rays, steps, getattr(orc, filt), mode, seed=3)
+            T = sf.sf_raymarch(vol, rd, steps, smp).cpu().numpy()
+            assert np.allclose(T, ref, rtol=1e-5, atol=1e-7), (filt, gmode, np.abs(T - ref).max())
+            assert np.array_equal(T, sf.sf_raymarch(volm, rd, steps, smp).cpu().numpy()), (filt, gmode)
+            if mode == orc.STOCHASTIC or filt == "LINEAR":
+                ref = orc.raymarch_emission(ogh, rays, steps, getattr(orc, filt), mode, seed=3)
+                L = sf.sf_raymarch_emission(volh, rd, steps, smp).cpu().numpy()
+                top = ref.max(axis=0)
+                assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6), (filt, gmode)
