@@ -208,17 +208,19 @@ inline int lane_group(int64_t n, int spp)
 // Launch grid of nb workgroups of `rays` rays (or queries) each, in runs of
 // 2^log_run workgroups per XCD (xcd_block).  A run is long enough that the
 // rays in flight on an XCD are neighbours and share its L2, and short enough
-// that each XCD gets at least eight of them from all over the image: with
+// that each XCD gets at least two of them, from two parts of the image: with
 // one contiguous eighth of the stream per XCD, those at the image's border
 // were done while the others still marched (512^3 cloud, 1 Mi rays, tricubic
 // and trilinear stochastic: 533 and 480 us in eighths, 500 and 435 in runs
-// of 16 Ki rays, 546 and 499 in runs of 4 Ki).
+// of 16 Ki rays, 546 and 499 in runs of 4 Ki).  128 x 128 pixels of 16
+// rays, trilinear stochastic, 256 steps: 324 us in eight runs per XCD (of 4 Ki
+// rays) and 223 in two (512^3), 151 and 99 (256^3).
 struct XcdGrid {
     uint32_t blocks, log_run;
     XcdGrid(uint32_t nb, uint32_t rays)
     {
         log_run = 0;
-        while ((rays << (log_run + 1)) <= 16384u && (nb >> (log_run + 1)) >= 64u)
+        while ((rays << (log_run + 1)) <= 16384u && (nb >> (log_run + 1)) >= 16u)
             ++log_run;
         const uint32_t step = 8u << log_run;
         blocks = (nb + step - 1) / step * step;
