@@ -274,10 +274,23 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
 // holds the taps of all its rays over up to STAGE_STEPS steps into LDS, as
 // binary32, and takes the taps from there.  A box that does not fit
 // (incoherent rays, sparse pixels) is tried over fewer steps and then given
-// up: those steps' taps are read from the grid.  Values and order of
-// summation are the same either way.
-constexpr int STAGE_UNITS = 640;   // 16 bytes each, per wavefront: 16 wavefronts share a CU's 160 KiB
+// up: those steps' taps are read from the grid, all loads of a step (or two
+// of its four planes) on their way before the first is used.  Values and order
+// of summation are the same either way.
+// One tap per step is always read from the grid (1 Mi rays x 256 steps, 256^3
+// binary16 cloud: 265 us, from boxes 768).  A box of eight taps per ray has to
+// serve four steps to be worth its wait, one of 64 taps a single one.
+// Units of 16 bytes per wavefront and wavefronts per SIMD, within 160 KiB per
+// CU: for two taps per axis 480 and five (1 Mi rays x 256 steps, before, 512^3
+// cloud: binary32 905 us, 320 and eight 1,382, 640 and four 938; binary16 946,
+// 1,176 and 990), for four 640 and four.
+template <int F>
+constexpr int STAGE_UNITS = F == NEAREST ? 0 : (Taps<F>::n == 2 ? 480 : 640);
+template <int F>
+constexpr int STAGE_WAVES = F == NEAREST ? 8 : (Taps<F>::n == 2 ? 5 : 4);
 constexpr int STAGE_STEPS = 4;
+template <int F>
+constexpr int STAGE_LEAST = Taps<F>::n == 2 ? 4 : 1;   // steps worth a box
 constexpr int STAGE_PAUSE = 8;     // steps read from the grid before a box is tried again
 
 __device__ __forceinline__ int wave_min(int v)
@@ -292,36 +305,90 @@ __device__ __forceinline__ int wave_min(int v)
 }
 __device__ __forceinline__ int wave_max(int v) { return ~wave_min(~v); }
 
-// Taps of one step read from the grid: row(by, cz) gives NT taps.
+// Taps of one step read from the grid: load() issues the loads of the rows of
+// planes c0.., value() makes the NT numbers of what came back for one row.
+// PLANES: planes to issue before the first row is used (the wait for the loads
+// is what such a step takes).
 template <int F, bool HALF>
-struct GridTaps {
-    static constexpr int NT = Taps<F>::n;
+struct GridVoxels {
+    static constexpr bool GRID = true;
+    static constexpr int NT = Taps<F>::n, PLANES = NT == 4 ? 2 : NT;
+    struct Raw {
+        uint32_t w[NT];
+    };
     const VolArgs &v;
     __amdgpu_buffer_rsrc_t rs;
     int x, y, z;     // first tap
-    bool inside;     // all taps, with two voxels to spare past each row (binary16 rows of four)
-    uint32_t e0;
-    __device__ __forceinline__ GridTaps(const VolArgs &vol, __amdgpu_buffer_rsrc_t r, const int i0[3]) : v(vol), rs(r)
+    __device__ __forceinline__ GridVoxels(const VolArgs &vol, __amdgpu_buffer_rsrc_t r, const int i0[3])
+        : v(vol), rs(r), x(i0[0] + Taps<F>::first), y(i0[1] + Taps<F>::first), z(i0[2] + Taps<F>::first)
     {
-        x = i0[0] + Taps<F>::first, y = i0[1] + Taps<F>::first, z = i0[2] + Taps<F>::first;
-        inside = false;
-        if constexpr (HALF && NT == 4)
-            inside = rows4_inside(v, i0);
-        e0 = ((uint32_t)z * (uint32_t)v.ny + (uint32_t)y) * (uint32_t)v.nx + (uint32_t)x;
     }
-    __device__ __forceinline__ void row(int by, int cz, float *t) const
+    template <int P>
+    __device__ __forceinline__ void load(int c0, Raw (&raw)[P][NT]) const
     {
-        if constexpr (HALF && NT == 4) {
-            if (inside) {
-                voxel_row4_half(rs, e0 + ((uint32_t)cz * (uint32_t)v.ny + (uint32_t)by) * (uint32_t)v.nx, t);
-                return;
-            }
-        }
+#pragma unroll
+        for (int cz = 0; cz < P; ++cz)
+#pragma unroll
+            for (int by = 0; by < NT; ++by)
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+                    raw[cz][by].w[a] = voxel_bits<HALF>(
+                        rs, voxel_offset_or_outside<HALF, false>(v, x + a, y + by, z + c0 + cz));
+    }
+    __device__ __forceinline__ void value(const Raw &r, float *t) const
+    {
 #pragma unroll
         for (int a = 0; a < NT; ++a)
-            t[a] = voxel<HALF>(rs, v, x + a, y + by, z + cz);
+            t[a] = bits_value<HALF>(r.w[a]);
     }
 };
+
+// Binary16 rows of four: one load per row where all of a step's taps lie
+// inside the grid (rows4_inside), else voxel by voxel into the same words, so
+// that the lanes of a wavefront at the grid's faces share what follows.
+template <int MODE>
+struct GridRows {
+    static constexpr bool GRID = true;
+    static constexpr int NT = 4, PLANES = MODE == BEFORE ? 4 : 2;
+    typedef voxel_words Raw;
+    const VolArgs &v;
+    __amdgpu_buffer_rsrc_t rs;
+    int x, y, z;     // first tap
+    bool inside;
+    __device__ __forceinline__ GridRows(const VolArgs &vol, __amdgpu_buffer_rsrc_t r, const int i0[3])
+        : v(vol), rs(r), x(i0[0] - 1), y(i0[1] - 1), z(i0[2] - 1), inside(rows4_inside(vol, i0))
+    {
+    }
+    template <int P>
+    __device__ __forceinline__ void load(int c0, Raw (&raw)[P][4]) const
+    {
+        if (inside) {
+            const uint32_t ys = (uint32_t)v.nx, zs = (uint32_t)v.ny * (uint32_t)v.nx;
+            const uint32_t e0 = (uint32_t)(z + c0) * zs + (uint32_t)y * ys + (uint32_t)x;
+#pragma unroll
+            for (int cz = 0; cz < P; ++cz)
+#pragma unroll
+                for (int by = 0; by < 4; ++by)
+                    raw[cz][by] = row4_load(rs, e0 + (uint32_t)cz * zs + (uint32_t)by * ys);
+        } else {
+#pragma unroll
+            for (int cz = 0; cz < P; ++cz)
+#pragma unroll
+                for (int by = 0; by < 4; ++by) {
+                    uint32_t h[4];
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        h[a] = voxel_bits<true>(
+                            rs, voxel_offset_or_outside<true, false>(v, x + a, y + by, z + c0 + cz));
+                    raw[cz][by] = {{h[0] | h[1] << 16, h[2] | h[3] << 16, 0u}, 0u};
+                }
+        }
+    }
+    __device__ __forceinline__ void value(const Raw &r, float *t) const { row4_values(r, t); }
+};
+
+template <int F, bool HALF, int MODE>
+using GridTaps = std::conditional_t<HALF && Taps<F>::n == 4, GridRows<MODE>, GridVoxels<F, HALF>>;
 
 // The staged box: nzb planes of nyb rows of u units of four voxels, from
 // voxel (x0, y0, z0).  A plane takes an odd number of units, so that the
@@ -330,10 +397,20 @@ struct StageBox {
     int x0, y0, z0, nyb, nzb, u, plane;
 };
 
+// Units of a box of nx x ny x nz voxels; more than MOST for a wider one.
+template <int MOST>
+__device__ __forceinline__ int box_units(int nx, int ny, int nz)
+{
+    const int u = (nx + 3) >> 2;
+    const int plane = u <= MOST && ny <= MOST ? u * ny | 1 : MOST + 1;
+    return plane <= MOST && nz <= MOST ? plane * nz : MOST + 1;
+}
+
 // Taps of one step read from the staged box.
 template <int F>
 struct StageTaps {
-    static constexpr int NT = Taps<F>::n;
+    static constexpr bool GRID = false;
+    static constexpr int NT = Taps<F>::n, PLANES = 1;
     const float *p;
     int ys, zs;   // voxels per row and per plane
     __device__ __forceinline__ StageTaps(const float *vox, const StageBox &b, const int i0[3])
@@ -343,25 +420,62 @@ struct StageTaps {
         p = vox + ((i0[2] + Taps<F>::first - b.z0) * zs + (i0[1] + Taps<F>::first - b.y0) * ys +
                    (i0[0] + Taps<F>::first - b.x0));
     }
-    __device__ __forceinline__ void row(int by, int cz, float *t) const
+    struct Raw {
+        float t[NT];
+    };
+    template <int P>
+    __device__ __forceinline__ void load(int c0, Raw (&raw)[P][NT]) const
     {
-        const float *r = p + (cz * zs + by * ys);
+#pragma unroll
+        for (int cz = 0; cz < P; ++cz)
+#pragma unroll
+            for (int by = 0; by < NT; ++by) {
+                const float *r = p + ((c0 + cz) * zs + by * ys);
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+                    raw[cz][by].t[a] = r[a];
+            }
+    }
+    __device__ __forceinline__ void value(const Raw &r, float *t) const
+    {
 #pragma unroll
         for (int a = 0; a < NT; ++a)
-            t[a] = r[a];
+            t[a] = r.t[a];
     }
 };
+
+// row(t, by, cz) for every row of the step's taps in order.
+template <int NT, typename T, typename Row>
+__device__ __forceinline__ void each_row(const T &taps, Row &&row)
+{
+    constexpr int PLANES = T::PLANES;
+#pragma unroll
+    for (int c0 = 0; c0 < NT; c0 += PLANES) {
+        typename T::Raw raw[PLANES][NT];
+        taps.load(c0, raw);
+        if constexpr (T::GRID)
+            __builtin_amdgcn_sched_barrier(0);   // all on their way
+#pragma unroll
+        for (int cz = 0; cz < PLANES; ++cz)
+#pragma unroll
+            for (int by = 0; by < NT; ++by) {
+                float t[NT];
+                taps.value(raw[cz][by], t);
+                row(t, by, c0 + cz);
+            }
+    }
+}
 
 // Copy the box into LDS (all 64 lanes), voxels outside the grid as 0: each
 // lane moves four voxels at a time, STAGE_LOADS loads in flight (a box is
 // mostly one or two rounds).  Returns the largest voxel by bit pattern (a
 // negative one, -0 and NaN above all others).
-template <bool HALF>
+template <int F, bool HALF>
 __device__ __forceinline__ uint32_t stage_box(const VolArgs &v, float *vox, const StageBox &b)
 {
     typedef uint32_t u32x2_2 __attribute__((ext_vector_type(2), aligned(2)));   // rows start at any voxel
     typedef uint32_t u32x4_4 __attribute__((ext_vector_type(4), aligned(4)));
-    constexpr int STAGE_LOADS = HALF ? 8 : 4, W = HALF ? 2 : 4;
+    constexpr int STAGE_LOADS = HALF && Taps<F>::n == 4 ? 8 : 4, W = HALF ? 2 : 4;
     const int units = b.plane * b.nzb;
     // q / plane and rem / u for q < 1024 and divisors up to 641
     const uint32_t invp = (uint32_t)(1048576.0f / (float)b.plane) + 1u, invu = (uint32_t)(1048576.0f / (float)b.u) + 1u;
@@ -422,28 +536,65 @@ __device__ __forceinline__ uint32_t stage_box(const VolArgs &v, float *vox, cons
 }
 
 // The march over every tap: eval(wx, wy, wz, taps, largest) once for each
-// step of this lane and wavefront that is not in a provably empty brick, in step order;
-// `largest` bounds the step's taps from above if they are all non-negative,
-// and is infinite otherwise.  Called by all lanes of a wavefront;
+// step of this lane and wavefront that is not in a provably empty brick, in step
+// order; `largest` bounds the step's taps from above if they are all
+// non-negative, and is infinite otherwise.  Called by all lanes of a wavefront;
 // `march` marks those with a ray.
-template <int F, bool HALF, bool OCC, typename Eval>
-__device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, bool march, int steps,
+template <int F, bool HALF, int MODE, bool OCC, typename Eval>
+__device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, bool march, bool together, int steps,
                                            const RaySplit &r, float *vox, Eval &&eval)
 {
-    constexpr int NT = Taps<F>::n;
-    constexpr int first = Taps<F>::first, last = F == NEAREST ? 1 : Taps<F>::first + Taps<F>::n - 1;
+    constexpr int first = Taps<F>::first, last = Taps<F>::first + Taps<F>::n - 1;
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(v.base), 0, (int)v.bytes, kBufferFlags);
     __amdgpu_buffer_rsrc_t rm;
     if constexpr (OCC)
         rm = occ_rsrc(v);
-    int mtry = STAGE_STEPS;   // steps of the next box
-    int pause = 0;            // steps still to be read from the grid without trying
-    // the wavefront's steps come in blocks of a box
-    for (int kb = STAGE_STEPS * r.first; kb < steps; kb += STAGE_STEPS * r.stride) {
-        const int k1 = min(kb + STAGE_STEPS, steps);
+    const auto weigh = [&](int i0[3], const float t[3], float wx[4], float wy[4], float wz[4]) {
+        if constexpr (F == NEAREST) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                i0[a] += t[a] >= 0.5f;
+        }
+        axis_weights<F>(t[0], wx);
+        axis_weights<F>(t[1], wy);
+        axis_weights<F>(t[2], wz);
+    };
+    int mtry = STAGE_STEPS;        // steps of the next box
+    // Rays that lie apart or take too long steps never try a box, and their
+    // wavefronts take the steps one by one, others in blocks of a box.
+    bool boxes = false;
+    if constexpr (STAGE_UNITS<F> > 0) {
+        int e[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            e[a] = Taps<F>::n + (int)((STAGE_LEAST<F> - 1) * __builtin_fminf(__builtin_fabsf(g.G[a]), 1024.0f));
+        boxes = together && __any(march && box_units<STAGE_UNITS<F>>(e[0], e[1], e[2]) <= STAGE_UNITS<F>);
+    }
+    const int block = boxes ? STAGE_STEPS : 1;
+    int direct = boxes ? 0 : 0x7fffffff;   // steps to read from the grid before a box is tried
+    int pause = STAGE_PAUSE;
+    for (int kb = block * r.first; kb < steps; kb += block * r.stride) {
+        const int k1 = min(kb + block, steps);
         for (int k = kb; k < k1;) {
-            const int m = min(pause > 0 ? min(pause, STAGE_STEPS) : mtry, k1 - k);
+            if (STAGE_UNITS<F> == 0 || direct > 0) {
+                if (march) {
+                    for (int kk = k; kk < k1; ++kk) {
+                        int i0[3];
+                        float t[3], wx[4], wy[4], wz[4];
+                        step_coords(g, (float)kk + 0.5f, i0, t);
+                        if constexpr (OCC) {
+                            if (brick_empty_clamped(rm, v, i0))
+                                continue;
+                        }
+                        weigh(i0, t, wx, wy, wz);
+                        eval(wx, wy, wz, GridTaps<F, HALF, MODE>(v, rs, i0), __builtin_inff());
+                    }
+                }
+                direct -= k1 - k;
+                break;
+            }
+            const int m = min(mtry, k1 - k);
             // brick bits of the m steps; a lane takes part while it has one to read
             uint32_t full = 0;
             if constexpr (OCC) {
@@ -464,17 +615,12 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
             if (!__any(full != 0u)) {   // nothing to read in these steps
                 k += m;
                 mtry = STAGE_STEPS;
-                pause = 0;
                 continue;
             }
-            StageBox b = {};
-            bool staged = false;
-            float largest = __builtin_inff();
-            if (pause > 0) {
-                pause -= m;
-            } else {
-                // the box of the wavefront's taps; a lane's cells lie between
-                // those of the first and the last step (positions are linear in k)
+            // the box of the wavefront's taps; a lane's cells lie between those
+            // of the first and the last step (positions are linear in k)
+            StageBox b;
+            {
                 float p[3];
                 int ia[3], ib[3], lo[3], hi[3];
                 step_pos(g, (float)k + 0.5f, p, ia);
@@ -486,55 +632,39 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
                 }
                 const int nx = hi[0] - lo[0] + 1 + last - first, ny = hi[1] - lo[1] + 1 + last - first,
                           nz = hi[2] - lo[2] + 1 + last - first;
-                const int u = (nx + 3) >> 2;
-                const int plane = u <= STAGE_UNITS && ny <= STAGE_UNITS ? u * ny | 1 : STAGE_UNITS + 1;
-                // A trilinear step has 8 taps to read where a tricubic one has 64, so
-                // its box may hold no more units per step than four steps' share:
-                // 4096 rays a voxel apart, 64^3 grid, 256 steps, before: 251 us with
-                // a full box for a single step, 97 with this line, 191 with each ray
-                // reading its own taps from one wavefront (tricubic: 433 with a full
-                // box, 1764 without).
-                const int room = NT == 4 ? STAGE_UNITS : STAGE_UNITS / STAGE_STEPS * m;
-                const bool fits = plane <= STAGE_UNITS && nz <= STAGE_UNITS && plane * nz <= room;
-                if (!fits) {
-                    if (m > 1)
+                const int units = box_units<STAGE_UNITS<F>>(nx, ny, nz);
+                if (units > STAGE_UNITS<F>) {
+                    if (m > STAGE_LEAST<F>) {
                         mtry = m >> 1;
-                    else
-                        pause = STAGE_PAUSE;
+                    } else {
+                        direct = pause;
+                        pause *= 2;
+                        mtry = STAGE_STEPS;
+                    }
                     continue;
                 }
                 // as many steps as can be next time if twice the box would fit
-                mtry = 2 * plane * nz <= STAGE_UNITS ? STAGE_STEPS : m;
+                mtry = 2 * units <= STAGE_UNITS<F> ? STAGE_STEPS : m;
+                pause = STAGE_PAUSE;
                 b.x0 = lo[0] + first, b.y0 = lo[1] + first, b.z0 = lo[2] + first;
-                b.nyb = ny, b.nzb = nz, b.u = u, b.plane = plane;
-                staged = true;
-                // Lanes read what others of the wavefront wrote: its LDS
-                // instructions run in order, the fences keep the compiler to it.
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                const uint32_t top = stage_box<HALF>(v, vox, b);
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                largest = top < 0x7f800000u ? __uint_as_float(top) : __builtin_inff();
+                b.nyb = ny, b.nzb = nz, b.u = (nx + 3) >> 2, b.plane = b.u * ny | 1;
             }
+            // Lanes read what others of the wavefront wrote: its LDS instructions
+            // run in order, the fences keep the compiler to it.
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t top = stage_box<F, HALF>(v, vox, b);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const float largest = top < 0x7f800000u ? __uint_as_float(top) : __builtin_inff();
             for (int j = 0; j < m; ++j) {
                 if (!((full >> j) & 1u))
                     continue;
                 int i0[3];
                 float t[3], wx[4], wy[4], wz[4];
                 step_coords(g, (float)(k + j) + 0.5f, i0, t);
-                if constexpr (F == NEAREST) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-                        i0[a] += t[a] >= 0.5f;
-                }
-                axis_weights<F>(t[0], wx);
-                axis_weights<F>(t[1], wy);
-                axis_weights<F>(t[2], wz);
-                if (staged)
-                    eval(wx, wy, wz, StageTaps<F>(vox, b, i0), largest);
-                else
-                    eval(wx, wy, wz, GridTaps<F, HALF>(v, rs, i0), largest);
+                weigh(i0, t, wx, wy, wz);
+                eval(wx, wy, wz, StageTaps<F>(vox, b, i0), largest);
             }
             k += m;
         }
@@ -558,22 +688,25 @@ __device__ __forceinline__ void march_taps(const VolArgs &v, const RayGeom &g, b
 // included), and no exponential is taken; where all of a step's do, f_k > 1/2
 // and only a_k is formed.  Which form a row takes depends on its own taps
 // alone.
-// 1 Mi rays x 256 steps through the 512^3 cloud, ms before (each ray reading
-// its own rows or taps) and now: tricubic after 8.1-9.5 -> 2.6, before
-// 6.1 -> 1.9, trilinear after 2.3 -> 1.1, before 2.2 -> 0.96; both tricubic
-// modes are bound by vector instructions (about 570 and 320 per 64-ray step)
-// and the LDS reads of the rows together.
+// 1 Mi rays x 256 steps through the 512^3 binary16 cloud with a mask of 8^3
+// bricks, ms before (each ray reading its own rows or taps) and now: tricubic
+// after 8.1 -> 2.1, before 5.3 -> 1.5, trilinear after 2.4 -> 0.91, before
+// 2.3 -> 0.78, nearest 0.50 -> 0.46 and 0.47 -> 0.42; both tricubic modes are
+// bound by vector instructions (about 570 and 320 per 64-ray step) and the LDS
+// reads of the rows together.
 template <int F, bool HALF, int MODE, bool OCC>
-__global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, SplitArgs sp)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STAGE_WAVES<F>))) void k_ray_det(RaymarchCall c, SplitArgs sp)
 {
-    __shared__ __attribute__((aligned(16))) float stage[4][4 * STAGE_UNITS];
+    // boxes, then the wavefronts' results
+    __shared__ __attribute__((aligned(16))) float stage[4][STAGE_UNITS<F> ? 4 * STAGE_UNITS<F> : 6 * 64];
     RaySplit r(sp);
     const int64_t i = r.i;
     RayGeom g = {};
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
+    const bool together = rays_together(g, st == 0, c.steps);
+    r.share(sp, together, c.steps);
     constexpr int NT = Taps<F>::n;
     const float dt = g.dt;
     CompSum tau;
@@ -583,21 +716,17 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, SplitArgs sp)
     const float dt2 = dt * dt;
     const float c2 = dt2 * -0x1.ffffe8p-2f, c3 = (dt2 * dt) * 0x1.5542bcp-3f, c4 = (dt2 * dt2) * -0x1.4d42c4p-5f;
     const float small = dt >= 0x1p-24f && dt <= 0x1p24f ? 0.0625f : 0.0f;
-    march_taps<F, HALF, OCC>(c.vol, g, st == 0, c.steps, r, stage[r.wave],
+    march_taps<F, HALF, MODE, OCC>(c.vol, g, st == 0, together, c.steps, r, stage[r.wave],
                              [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
         float acc = 0.0f;
         if constexpr (MODE == BEFORE) {
+            each_row<NT>(taps, [&](const float *t, int by, int cz) {
+                float row = 0.0f;
 #pragma unroll
-            for (int cz = 0; cz < NT; ++cz)
-#pragma unroll
-                for (int by = 0; by < NT; ++by) {
-                    float t[NT], row = 0.0f;
-                    taps.row(by, cz, t);
-#pragma unroll
-                    for (int ax = 0; ax < NT; ++ax)
-                        row = __builtin_fmaf(wx[ax], t[ax], row);
-                    acc = __builtin_fmaf(wy[by] * wz[cz], row, acc);
-                }
+                for (int ax = 0; ax < NT; ++ax)
+                    row = __builtin_fmaf(wx[ax], t[ax], row);
+                acc = __builtin_fmaf(wy[by] * wz[cz], row, acc);
+            });
             tau.add(acc);
         } else {
             auto poly_row = [&](const float *t) {
@@ -612,15 +741,10 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, SplitArgs sp)
                 return row;
             };
             // (`largest` is uniform, and so mostly is the outcome)
-            if (largest * dt < small) {
-#pragma unroll
-                for (int cz = 0; cz < NT; ++cz)
-#pragma unroll
-                    for (int by = 0; by < NT; ++by) {
-                        float t[NT];
-                        taps.row(by, cz, t);
-                        acc = __builtin_fmaf(wy[by] * wz[cz], poly_row(t), acc);
-                    }
+            if (!taps.GRID && largest * dt < small) {
+                each_row<NT>(taps, [&](const float *t, int by, int cz) {
+                    acc = __builtin_fmaf(wy[by] * wz[cz], poly_row(t), acc);
+                });
                 Tp.mul_one_minus(acc);
                 return;
             }
@@ -629,32 +753,28 @@ __global__ __launch_bounds__(256) void k_ray_det(RaymarchCall c, SplitArgs sp)
 #pragma unroll
             for (int ax = 1; ax < NT; ++ax)
                 wsum += wx[ax];
+            each_row<NT>(taps, [&](const float *t, int by, int cz) {
+                float row = 0.0f, rowf = 0.0f;
+                uint32_t top = __float_as_uint(t[0]);
 #pragma unroll
-            for (int cz = 0; cz < NT; ++cz)
+                for (int ax = 1; ax < NT; ++ax)
+                    top = max(top, __float_as_uint(t[ax]));
+                if (top < 0x7f800000u && __uint_as_float(top) * dt < small) {
+                    row = poly_row(t);
+                    rowf = wsum - row;
+                } else {
 #pragma unroll
-                for (int by = 0; by < NT; ++by) {
-                    float t[NT], row = 0.0f, rowf = 0.0f;
-                    taps.row(by, cz, t);
-                    uint32_t top = __float_as_uint(t[0]);
-#pragma unroll
-                    for (int ax = 1; ax < NT; ++ax)
-                        top = max(top, __float_as_uint(t[ax]));
-                    if (top < 0x7f800000u && __uint_as_float(top) * dt < small) {
-                        row = poly_row(t);
-                        rowf = wsum - row;
-                    } else {
-#pragma unroll
-                        for (int ax = 0; ax < NT; ++ax) {
-                            float e, m;
-                            exp_neg_pair(t[ax] * dt, e, m);
-                            row = __builtin_fmaf(wx[ax], m, row);
-                            rowf = __builtin_fmaf(wx[ax], e, rowf);
-                        }
+                    for (int ax = 0; ax < NT; ++ax) {
+                        float e, m;
+                        exp_neg_pair(t[ax] * dt, e, m);
+                        row = __builtin_fmaf(wx[ax], m, row);
+                        rowf = __builtin_fmaf(wx[ax], e, rowf);
                     }
-                    const float wyz = wy[by] * wz[cz];
-                    acc = __builtin_fmaf(wyz, row, acc);
-                    accf = __builtin_fmaf(wyz, rowf, accf);
                 }
+                const float wyz = wy[by] * wz[cz];
+                acc = __builtin_fmaf(wyz, row, acc);
+                accf = __builtin_fmaf(wyz, rowf, accf);
+            });
             if (accf < 0.5f)
                 Tp.mul(accf, 0.0f);
             else
@@ -850,71 +970,76 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
     }
 }
 
-// Deterministic emission (march_taps: 262,144 rays x 256 steps of the 512^3
-// fire, tricubic after 9.9 -> 3.7 ms, bound by the transcendental unit, and
-// before 3.4 -> 1.9 ms): E_k = B(sum_i w_i T_i) before shading,
+// Deterministic emission (march_taps: 1 Mi rays x 256 steps of the 512^3
+// binary16 fire with a mask of 8^3 bricks, tricubic after 28.5 -> 10.2 ms,
+// bound by the transcendental unit, and before 5.4 -> 1.7 ms): E_k = B(sum_i w_i T_i) before shading,
 // sum_i w_i B(T_i) after; binary32 weights and per-step sums of positive
 // terms, steps summed with compensation.
 template <int F, bool HALF, int MODE, bool OCC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_emit_det(RaymarchCall c, SplitArgs sp)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STAGE_WAVES<F>))) void k_emit_det(RaymarchCall c, SplitArgs sp)
 {
-    __shared__ __attribute__((aligned(16))) float stage[4][4 * STAGE_UNITS];
+    // boxes, then the wavefronts' results
+    __shared__ __attribute__((aligned(16))) float stage[4][STAGE_UNITS<F> ? 4 * STAGE_UNITS<F> : 6 * 64];
     RaySplit r(sp);
     const int64_t i = r.i;
     RayGeom g = {};
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
+    const bool together = rays_together(g, st == 0, c.steps);
+    r.share(sp, together, c.steps);
     constexpr int NT = Taps<F>::n;
     CompSum acc[3];
     acc[0].init();
     acc[1].init();
     acc[2].init();
-    march_taps<F, HALF, OCC>(c.vol, g, st == 0, c.steps, r, stage[r.wave],
+    march_taps<F, HALF, MODE, OCC>(c.vol, g, st == 0, together, c.steps, r, stage[r.wave],
                              [&](const float *wx, const float *wy, const float *wz, auto taps, float largest) {
-        float e[3] = {0.0f, 0.0f, 0.0f};
-        // exact after: a plane at a time and its rows one by one, since all 64
-        // taps side by side take more registers than there are
-        auto add_taps = [&](auto cool) {
-#pragma unroll(MODE == BEFORE ? NT : 1)
-            for (int cz = 0; cz < NT; ++cz) {
-                const float wzc = MODE == BEFORE || NT == 1 ? wz[cz] : (NT == 2 ? (cz == 0 ? wz[0] : wz[1])
-                                                              : (cz < 2 ? (cz == 0 ? wz[0] : wz[1]) : (cz == 2 ? wz[2] : wz[3])));
+        if constexpr (MODE == BEFORE) {
+            float T = 0.0f, B[3];
+            each_row<NT>(taps, [&](const float *t, int by, int cz) {
+                const float wyz = wy[by] * wz[cz];
 #pragma unroll
-                for (int by = 0; by < NT; ++by) {
-                    float t[NT];
-                    taps.row(by, cz, t);
-                    const float wyz = wy[by] * wzc;
+                for (int ax = 0; ax < NT; ++ax)
+                    T = __builtin_fmaf(wx[ax] * wyz, t[ax], T);
+            });
+            planck3(T, B);
+            acc[0].add(B[0]);
+            acc[1].add(B[1]);
+            acc[2].add(B[2]);
+        } else {
+            float e[3] = {0.0f, 0.0f, 0.0f};
+            // a plane at a time and its rows one by one, since all 64 taps side
+            // by side take more registers than there are
+            auto add_taps = [&](auto cool) {
+#pragma unroll 1
+                for (int cz = 0; cz < NT; ++cz) {
+                    const float wzc = NT == 1 ? wz[0] : (NT == 2 ? (cz == 0 ? wz[0] : wz[1])
+                                                  : (cz < 2 ? (cz == 0 ? wz[0] : wz[1]) : (cz == 2 ? wz[2] : wz[3])));
+                    typename decltype(taps)::Raw raw[1][NT];
+                    taps.load(cz, raw);
 #pragma unroll
-                    for (int ax = 0; ax < NT; ++ax) {
-                        const float w = wx[ax] * wyz;
-                        if constexpr (MODE == BEFORE) {
-                            e[0] = __builtin_fmaf(w, t[ax], e[0]);
-                        } else {
+                    for (int by = 0; by < NT; ++by) {
+                        float t[NT];
+                        taps.value(raw[0][by], t);
+                        const float wyz = wy[by] * wzc;
+#pragma unroll
+                        for (int ax = 0; ax < NT; ++ax) {
+                            const float w = wx[ax] * wyz;
                             float B[3];
                             planck3<decltype(cool)::value>(t[ax], B);
                             e[0] = __builtin_fmaf(w, B[0], e[0]);
                             e[1] = __builtin_fmaf(w, B[1], e[1]);
                             e[2] = __builtin_fmaf(w, B[2], e[2]);
                         }
-                    }
-                    if constexpr (MODE != BEFORE)
                         __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-            }
-        };
-        if (MODE == BEFORE || largest < PLANCK_HOT)
-            add_taps(std::true_type{});
-        else
-            add_taps(std::false_type{});
-        if constexpr (MODE == BEFORE) {
-            float B[3];
-            planck3(e[0], B);
-            acc[0].add(B[0]);
-            acc[1].add(B[1]);
-            acc[2].add(B[2]);
-        } else {
+            };
+            if (!taps.GRID && largest < PLANCK_HOT)
+                add_taps(std::true_type{});
+            else
+                add_taps(std::false_type{});
             acc[0].add(e[0]);
             acc[1].add(e[1]);
             acc[2].add(e[2]);

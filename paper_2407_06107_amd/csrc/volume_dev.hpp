@@ -53,7 +53,7 @@ __device__ __forceinline__ float voxel_load(__amdgpu_buffer_rsrc_t rs, uint32_t 
 
 // Whether the 4x4x4 taps around raster cell i0 (offsets -1..2 per axis) lie
 // inside the grid with two voxels to spare past each x row, so that
-// voxel_row4_half may read every row.
+// row4_load may read every row.
 __device__ __forceinline__ bool rows4_inside(const VolArgs &v, const int i0[3])
 {
     return i0[0] - 1 >= 0 && i0[0] + 4 < v.nx && i0[1] - 1 >= 0 && i0[1] + 2 < v.ny && i0[2] - 1 >= 0 &&
@@ -62,14 +62,22 @@ __device__ __forceinline__ bool rows4_inside(const VolArgs &v, const int i0[3])
 
 // The four binary16 voxels e..e+3 (e a voxel index; a row of the grid that
 // extends at least two voxels past e+3) read with one 12-byte load at the
-// 4-byte boundary at or below voxel e and a funnel shift.
-__device__ __forceinline__ void voxel_row4_half(__amdgpu_buffer_rsrc_t rs, uint32_t e, float sg[4])
+// 4-byte boundary at or below voxel e, and taken from it by a funnel shift.
+struct voxel_words {
+    uint32_t w[3], sh;
+};
+
+__device__ __forceinline__ voxel_words row4_load(__amdgpu_buffer_rsrc_t rs, uint32_t e)
 {
     typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
     const u32x3 w = __builtin_bit_cast(u32x3, __builtin_amdgcn_raw_buffer_load_b96(rs, (2u * e) & ~3u, 0, 0));
-    const uint32_t sh = (e & 1u) * 16u;   // the row starts in the high half of its first word
-    const uint32_t d0 = __builtin_amdgcn_alignbit(w.y, w.x, sh);
-    const uint32_t d1 = __builtin_amdgcn_alignbit(w.z, w.y, sh);
+    return {{w.x, w.y, w.z}, (e & 1u) * 16u};   // the row starts in the high half of its first word where e is odd
+}
+
+__device__ __forceinline__ void row4_values(const voxel_words &r, float sg[4])
+{
+    const uint32_t d0 = __builtin_amdgcn_alignbit(r.w[1], r.w[0], r.sh);
+    const uint32_t d1 = __builtin_amdgcn_alignbit(r.w[2], r.w[1], r.sh);
     sg[0] = half_bits_to_float((uint16_t)d0);
     sg[1] = half_bits_to_float((uint16_t)(d0 >> 16));
     sg[2] = half_bits_to_float((uint16_t)d1);

@@ -502,3 +502,33 @@ def test_march_shares_its_steps_among_wavefronts(sf, orc, cloud48, kind, steps):
                 L = sf.sf_raymarch_emission(volh, rd, steps, smp).cpu().numpy()
                 top = ref.max(axis=0)
                 assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6), (filt, gmode)
+
+
+# fewer than 16 steps are not split over wavefronts: the same rays with their
+# neighbours (staged boxes) and among strangers (taps from the grid)
+@pytest.mark.parametrize("shape", [(5, 2, 3), (13, 9, 7), (40, 36, 44)])
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("steps", [3, 15])
+def test_every_tap_march_does_not_depend_on_the_ray_beside(sf, cloud48, shape, dtype, steps):
+    """Values and order of summation are the same wherever the taps come from:
+    bit-identical, before and exact after, the emission too."""
+    from paper_2407_06107_amd import inputs
+    _case("every_tap_neighbours", shape, np.dtype(dtype).name, steps)
+    nz, ny, nx = shape
+    data = np.ascontiguousarray(cloud48[4:4 + nz, 6:6 + ny, 2:2 + nx].astype(dtype))
+    hot = np.where(data > 0, 800 + 5200 * np.sqrt(data / max(float(data.max()), 1e-3)), 0).astype(dtype)
+    rays = inputs.ortho_rays(64, 16, side=1.0, seed=nx)
+    rays[::7, 6] -= 0.2
+    rays[::5, 7] += 0.3
+    order = np.arange(len(rays)).reshape(64, -1).T.reshape(-1)   # a wavefront's rays from all over the image
+    near = torch.from_numpy(rays).cuda()
+    apart = torch.from_numpy(np.ascontiguousarray(rays[order])).cuda()
+    for march, values in ((sf.sf_raymarch, data), (sf.sf_raymarch_emission, hot)):
+        for brick in (None, 2):
+            vol = sf.Volume(torch.from_numpy(values).cuda(), side=1.0, brick_log2=brick)
+            for filt in (sf.SF_NEAREST, sf.SF_LINEAR, sf.SF_BSPLINE3):
+                for mode in (sf.SF_BEFORE, sf.SF_AFTER_EXACT):
+                    smp = sf.sampling(filt, mode)
+                    a = march(vol, near, steps, smp).cpu().numpy()
+                    b = march(vol, apart, steps, smp).cpu().numpy()
+                    assert np.array_equal(a[order], b), (march.__name__, brick, filt, mode)
