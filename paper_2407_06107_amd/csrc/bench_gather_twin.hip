@@ -5,12 +5,13 @@
 // memory system sets for that kernel's access pattern.  It is the timed
 // kernel (k_ray_stoch for the cubic B-spline, binary16 grid, independent
 // uniforms, occupancy mask, power-of-two addressing) with the random pick
-// taken out: the same ray setup, XCD block mapping, per-step raster position,
-// brick words loaded a step ahead, pipelined binary16 voxel load (one per
-// step, past the grid's end in an empty brick) and result write; the tap of step k on axis a is
-// i0 - 1 + ((k >> 2a) & 3), which walks all 64 taps of the 4 x 4 x 4 range
-// the B-spline pick draws from (so the gathers spread over the same cache
-// footprint), and the densities are added in a plain binary32 sum.
+// taken out: the same launch shape, share of a ray's steps per wavefront, XCD
+// block mapping, ray setup, per-step raster position, brick words loaded a
+// step ahead, pipelined binary16 voxel load (one per step, past the grid's end
+// in an empty brick), sums that meet in LDS and result write; the tap of step
+// k on axis a is i0 - 1 + ((k >> 2a) & 3), which walks all 64 taps of the
+// 4 x 4 x 4 range the B-spline pick draws from (so the gathers spread over the
+// same cache footprint), and the densities are added in a plain binary32 sum.
 // t(twin) / t(real kernel) on the same launch is the fraction of this gather
 // ceiling the real kernel reaches.
 #include "volume_dev.hpp"
@@ -19,17 +20,16 @@
 
 namespace sfk {
 
-__global__ __launch_bounds__(256) void k_ray_gather_twin(RaymarchCall c, uint32_t log_run)
+__global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_gather_twin(RaymarchCall c, SplitArgs sp)
 {
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, log_run) * 256 + threadIdx.x;
-    if (i >= c.n)
-        return;
-    RayGeom g;
-    const int st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    if (st != 0) {
-        c.T[i] = st == 1 ? 1.0f : __builtin_nanf("");
-        return;
-    }
+    __shared__ float part[MAX_SPLIT_WAVES][64];
+    RaySplit r(sp);
+    const int64_t i = r.i;
+    RayGeom g = {};
+    int st = 3;   // no ray
+    if (i < c.n)
+        st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
+    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t rm = occ_rsrc(c.vol);
@@ -40,34 +40,47 @@ __global__ __launch_bounds__(256) void k_ray_gather_twin(RaymarchCall c, uint32_
         uint32_t word, bit;
     };
     float tau = 0.0f;
-    uint32_t pend;
-    float kh = 0.5f;
-    auto step = [&](int k, const At &cur, At &nxt) {
-        const bool empty = __builtin_amdgcn_ubfe(cur.word, cur.bit, 1u) != 0u;
-        kh += 1.0f;
-        step_pos(g, kh, nxt.p, nxt.i0);
-        nxt.word = brick_word(rm, c.vol, nxt.i0, nxt.bit);
-        tau += bits_value<true>(pend);     // step k - 1
-        uint32_t off = kOut;
-        if (!empty)
-            off = voxel_offset_or_outside<true, true>(c.vol, cur.i0[0] + (k & 3) - 1, cur.i0[1] + ((k >> 2) & 3) - 1,
-                                                      cur.i0[2] + ((k >> 4) & 3) - 1);
-        pend = voxel_bits<true>(rs, off);  // step k
-    };
-    At a, b;
-    step_pos(g, kh, a.p, a.i0);
-    a.word = brick_word(rm, c.vol, a.i0, a.bit);
-    __builtin_amdgcn_sched_barrier(0);
-    pend = voxel_bits<true>(rs, kOut | (a.bit >> 31));
-    int k = 0;
-    for (; k + 1 < c.steps; k += 2) {
-        step(k, a, b);
-        step(k + 1, b, a);
+    if (st == 0) {
+        uint32_t pend;
+        float kh = (float)r.first + 0.5f;
+        const float dk = (float)r.stride;
+        auto step = [&](int k, const At &cur, At &nxt) {
+            const bool empty = __builtin_amdgcn_ubfe(cur.word, cur.bit, 1u) != 0u;
+            kh += dk;
+            step_pos(g, kh, nxt.p, nxt.i0);
+            nxt.word = brick_word(rm, c.vol, nxt.i0, nxt.bit);
+            tau += bits_value<true>(pend);     // the step before
+            uint32_t off = kOut;
+            if (!empty)
+                off = voxel_offset_or_outside<true, true>(c.vol, cur.i0[0] + (k & 3) - 1,
+                                                          cur.i0[1] + ((k >> 2) & 3) - 1,
+                                                          cur.i0[2] + ((k >> 4) & 3) - 1);
+            pend = voxel_bits<true>(rs, off);  // step k
+        };
+        At a, b;
+        step_pos(g, kh, a.p, a.i0);
+        a.word = brick_word(rm, c.vol, a.i0, a.bit);
+        __builtin_amdgcn_sched_barrier(0);
+        pend = voxel_bits<true>(rs, kOut | (a.bit >> 31));
+        int k = r.first;
+        for (; k + r.stride < c.steps; k += 2 * r.stride) {
+            step(k, a, b);
+            step(k + r.stride, b, a);
+        }
+        if (k < c.steps)
+            step(k, a, b);
+        tau += bits_value<true>(pend);
     }
-    if (k < c.steps)
-        step(k, a, b);
-    tau += bits_value<true>(pend);
-    c.T[i] = expf(-(g.dt * tau));
+    if (sp.log_split) {
+        part[r.wave][r.lane] = tau;
+        __syncthreads();
+        if (r.part == 0)
+            for (int q = 1; q < r.parts; ++q)
+                tau += part[r.wave + q][r.lane];
+    }
+    if (r.part != 0 || st == 3)
+        return;
+    c.T[i] = st == 0 ? expf(-(g.dt * tau)) : (st == 1 ? 1.0f : __builtin_nanf(""));
 }
 
 }  // namespace sfk
@@ -117,7 +130,7 @@ extern "C" int sfb_gather_twin(const void *grid, int32_t nx, int32_t ny, int32_t
     c.steps = steps;
     c.spp = 1;
     c.T = T;
-    const sfk::XcdGrid xg((uint32_t)((n + 255) / 256), 256);
-    sfk::k_ray_gather_twin<<<dim3(xg.blocks), dim3(256), 0, (hipStream_t)stream>>>(c, xg.log_run);
+    const sfk::SplitGrid sg(n, steps, 4, sfk::STOCH_LANES);
+    sfk::k_ray_gather_twin<<<dim3(sg.blocks), dim3(sg.lanes), 0, (hipStream_t)stream>>>(c, sg.args);
     return (int)hipGetLastError();
 }

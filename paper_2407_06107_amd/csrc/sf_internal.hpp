@@ -227,6 +227,52 @@ struct XcdGrid {
     }
 };
 
+// The wavefronts that share a ray (RaySplit) and the runs of workgroups on an
+// XCD (xcd_block).
+struct SplitArgs {
+    uint32_t log_run, log_split, log_apart;
+};
+
+constexpr int MAX_SPLIT_WAVES = 16;
+
+// Launch shape of a march of n rays: workgroups of `lanes` lanes, each ray
+// over 2^log_split wavefronts, until there are `wanted` lanes, 2^most
+// wavefronts per ray or fewer than 16 steps each.  Stochastic marches (`once`)
+// read one voxel a step and want 2^18 lanes, half of what the chip holds, and
+// one split up to 2 Mi rays; marches over every tap want more, the more taps (a
+// staged box is a long wait).  Rays that lie apart (rays_together) are split
+// only up to `apart` lanes, while all wavefronts launched fit the chip at once
+// (past that, those without steps would keep others out).  256 steps, 256^3
+// binary16 cloud, trilinear, us with a quarter of `wanted`, with it and with
+// four times it: stochastic, 64 x 64 pixels of 16 rays 53, 38 and 40, 65,536 random
+// rays 159, 160 and 186; exact after, 128 x 128 pixels of 16 501, 298 and 298.
+// 65,536 random rays without the limit of `apart`: exact after 615, 554 with it.
+struct MarchLanes {
+    int64_t wanted, apart;
+    bool once;
+};
+constexpr MarchLanes STOCH_LANES = {1 << 18, 1 << 17, true};
+struct SplitGrid {
+    uint32_t blocks, lanes;
+    SplitArgs args;
+    SplitGrid(int64_t n, int steps, uint32_t most, const MarchLanes &m)
+    {
+        uint32_t log_split = 0, log_apart = 0;
+        while (log_split < most && (steps >> (log_split + 1)) >= 8 &&
+               ((n << log_split) < m.wanted || (m.once && log_split == 0 && n < (1 << 21))))
+            ++log_split;
+        while (log_apart < log_split && (n << (log_apart + 1)) <= m.apart)
+            ++log_apart;
+        if ((n << log_split) > (1 << 19))
+            log_apart = log_split;
+        lanes = 64u << (log_split > 2 ? log_split : 2);
+        const uint32_t rays = lanes >> log_split;
+        const XcdGrid xg((uint32_t)((n + rays - 1) / rays), rays);
+        blocks = xg.blocks;
+        args = {xg.log_run, log_split, log_apart};
+    }
+};
+
 hipError_t launch_raymarch(const RaymarchCall &c, hipStream_t s);
 hipError_t launch_emission(const RaymarchCall &c, hipStream_t s);
 hipError_t launch_build_occupancy(const VolArgs &v, uint32_t *occ, hipStream_t s);

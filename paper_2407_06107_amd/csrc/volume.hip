@@ -80,62 +80,6 @@ __device__ __forceinline__ void planck3(float T, float B[3])
 }
 
 // ---------------------------------------------------------------- ray march
-// A ray's steps are split over 2^log_split wavefronts of a workgroup (1 for
-// launches with rays enough): 64 rays have as many neighbouring wavefronts, which
-// take their steps (or blocks of steps) in turn, and whose sums meet in LDS in
-// wavefront order.  Few rays then still fill the chip, and a launch of many ends
-// with shorter wavefronts (SplitGrid).  In turn, not a stretch of the ray each:
-// the rays on their way stay at one depth together and find their voxels in the
-// caches.  Rays that lie apart share no lines, and more of them on their way at
-// once find fewer: those are split over 2^log_apart wavefronts only, and the
-// group's others have no steps.  65,536 rays x 256 steps, trilinear stochastic, 256^3
-// binary16 cloud: 64 x 64 pixels of 16 rays 97 us unsplit, 57 in 16 stretches and 38
-// in turns of four; random rays 159, 242 and 160 us.
-struct SplitArgs {
-    uint32_t log_run, log_split, log_apart;
-};
-
-struct RaySplit {
-    int64_t i;         // ray
-    int wave, lane;
-    int part, parts;   // the wavefront's place among those of its rays
-    int first, stride; // its steps (or blocks): first, first + stride, ..
-    __device__ __forceinline__ RaySplit(const SplitArgs &sp)
-    {
-        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        lane = threadIdx.x & 63;
-        parts = 1 << sp.log_split;
-        part = wave & (parts - 1);
-        first = part;
-        stride = parts;
-        i = (int64_t)xcd_block(blockIdx.x, sp.log_run) * (blockDim.x >> sp.log_split) +
-            (((wave >> sp.log_split) << 6) | lane);
-    }
-    __device__ __forceinline__ void share(const SplitArgs &sp, bool together, int steps)
-    {
-        stride = 1 << (together ? sp.log_split : sp.log_apart);
-        first = part < stride ? part : steps;
-    }
-};
-
-// Whether the wavefront's rays lie together: of the lanes that march beside
-// one that does, three in four are within 16 voxels of it half-way.  All lanes
-// call it; the wavefronts of the same rays find the same.
-__device__ __forceinline__ bool rays_together(const RayGeom &g, bool march, int steps)
-{
-    float p[3];
-    int i0[3];
-    step_pos(g, 0.5f * (float)steps, p, i0);
-    const bool pair = march & (__builtin_amdgcn_update_dpp(0, (int)march, 0x111, 0xf, 0xf, false) != 0);   // row_shr:1
-    bool near = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        near &= (uint32_t)(i0[a] - __builtin_amdgcn_update_dpp(0, i0[a], 0x111, 0xf, 0xf, false) + 16) <= 32u;
-    return 4 * __popcll(__ballot(pair & near)) >= 3 * __popcll(__ballot(pair));
-}
-
-constexpr int MAX_SPLIT_WAVES = 16;
-
 template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
 __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall c, SplitArgs sp)
 {
@@ -1285,44 +1229,10 @@ hipError_t launch_build_occupancy(const VolArgs &v, uint32_t *occ, hipStream_t s
 // ---------------------------------------------------------------- launchers
 static uint32_t blocks_for(int64_t n) { return (uint32_t)((n + 255) / 256); }
 
-// Launch shape of a march of n rays: workgroups of `lanes` lanes, each ray
-// over 2^log_split wavefronts, until there are `wanted` lanes, 2^most
-// wavefronts per ray or fewer than 16 steps each.  Stochastic marches (`once`)
-// read one voxel a step and want 2^18 lanes, half of what the chip holds, and
-// one split up to 2 Mi rays; marches over every tap want more, the more taps (a
-// staged box is a long wait).  Rays that lie apart (rays_together) are split
-// only up to `apart` lanes, while all wavefronts launched fit the chip at once
-// (past that, those without steps would keep others out).
-struct MarchLanes {
-    int64_t wanted, apart;
-    bool once;
-};
-constexpr MarchLanes STOCH_LANES = {1 << 18, 1 << 17, true};
 template <int F>
 constexpr MarchLanes DET_LANES = F == NEAREST   ? MarchLanes{1 << 19, 1 << 17, false}
                                  : F == LINEAR ? MarchLanes{1 << 20, 1 << 16, false}
                                                : MarchLanes{1 << 21, 1 << 18, false};
-
-struct SplitGrid {
-    uint32_t blocks, lanes;
-    SplitArgs args;
-    SplitGrid(int64_t n, int steps, uint32_t most, const MarchLanes &m)
-    {
-        uint32_t log_split = 0, log_apart = 0;
-        while (log_split < most && (steps >> (log_split + 1)) >= 8 &&
-               ((n << log_split) < m.wanted || (m.once && log_split == 0 && n < (1 << 21))))
-            ++log_split;
-        while (log_apart < log_split && (n << (log_apart + 1)) <= m.apart)
-            ++log_apart;
-        if ((n << log_split) > (1 << 19))
-            log_apart = log_split;
-        lanes = 64u << (log_split > 2 ? log_split : 2);
-        const uint32_t rays = lanes >> log_split;
-        const XcdGrid xg((uint32_t)((n + rays - 1) / rays), rays);
-        blocks = xg.blocks;
-        args = {xg.log_run, log_split, log_apart};
-    }
-};
 
 template <int F, bool HALF, bool OCC, bool P2>
 static void launch_ray_fo(const RaymarchCall &c, hipStream_t s)

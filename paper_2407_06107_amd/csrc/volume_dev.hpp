@@ -1,7 +1,8 @@
 // Device helpers of the 3-D paths, shared by the ray-march kernels of libsf
 // and by the benchmark's gather-only copy of the stochastic march: voxel
 // addressing through a raw buffer resource, the per-step raster position,
-// the brick occupancy test and the per-axis tap picks.
+// the wavefronts that share a ray, the brick occupancy test and the per-axis
+// tap picks.
 #pragma once
 #include "sf_device.hpp"
 #include "sf_internal.hpp"
@@ -127,6 +128,56 @@ __device__ __forceinline__ void step_coords(const RayGeom &g, float kh, int i0[3
     float p[3];
     step_pos(g, kh, p, i0);
     step_frac(p, i0, t);
+}
+
+// A ray's steps are split over 2^log_split wavefronts of a workgroup (1 for
+// launches with rays enough): 64 rays have as many neighbouring wavefronts, which
+// take their steps (or blocks of steps) in turn, and whose sums meet in LDS in
+// wavefront order.  Few rays then still fill the chip, and a launch of many ends
+// with shorter wavefronts (SplitGrid).  In turn, not a stretch of the ray each:
+// the rays on their way stay at one depth together and find their voxels in the
+// caches.  Rays that lie apart share no lines, and more of them on their way at
+// once find fewer: those are split over 2^log_apart wavefronts only, and the
+// group's others have no steps.  65,536 rays x 256 steps, trilinear stochastic, 256^3
+// binary16 cloud: 64 x 64 pixels of 16 rays 97 us unsplit, 57 in 16 stretches and 38
+// in turns of four; random rays 159, 242 and 160 us.
+struct RaySplit {
+    int64_t i;         // ray
+    int wave, lane;
+    int part, parts;   // the wavefront's place among those of its rays
+    int first, stride; // its steps (or blocks): first, first + stride, ..
+    __device__ __forceinline__ RaySplit(const SplitArgs &sp)
+    {
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        lane = threadIdx.x & 63;
+        parts = 1 << sp.log_split;
+        part = wave & (parts - 1);
+        first = part;
+        stride = parts;
+        i = (int64_t)xcd_block(blockIdx.x, sp.log_run) * (blockDim.x >> sp.log_split) +
+            (((wave >> sp.log_split) << 6) | lane);
+    }
+    __device__ __forceinline__ void share(const SplitArgs &sp, bool together, int steps)
+    {
+        stride = 1 << (together ? sp.log_split : sp.log_apart);
+        first = part < stride ? part : steps;
+    }
+};
+
+// Whether the wavefront's rays lie together: of the lanes that march beside
+// one that does, three in four are within 16 voxels of it half-way.  All lanes
+// call it; the wavefronts of the same rays find the same.
+__device__ __forceinline__ bool rays_together(const RayGeom &g, bool march, int steps)
+{
+    float p[3];
+    int i0[3];
+    step_pos(g, 0.5f * (float)steps, p, i0);
+    const bool pair = march & (__builtin_amdgcn_update_dpp(0, (int)march, 0x111, 0xf, 0xf, false) != 0);   // row_shr:1
+    bool near = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        near &= (uint32_t)(i0[a] - __builtin_amdgcn_update_dpp(0, i0[a], 0x111, 0xf, 0xf, false) + 16) <= 32u;
+    return 4 * __popcll(__ballot(pair & near)) >= 3 * __popcll(__ballot(pair));
 }
 
 // Byte offset of voxel (x, y, z), or for a tap outside the grid an offset at

@@ -532,3 +532,38 @@ def test_every_tap_march_does_not_depend_on_the_ray_beside(sf, cloud48, shape, d
                     a = march(vol, near, steps, smp).cpu().numpy()
                     b = march(vol, apart, steps, smp).cpu().numpy()
                     assert np.array_equal(a[order], b), (march.__name__, brick, filt, mode)
+
+
+# sixteen, eight, four, two wavefronts per ray, and one
+@pytest.mark.parametrize("n", [1, 1000, 20000, 40000, 100000, (1 << 21) + 1])
+@pytest.mark.parametrize("steps", [16, 65])
+def test_gather_twin_takes_every_step_once(sf, n, steps):
+    """The benchmark's twin of the timed march in a constant medium, through
+    cells whose taps are all inside: T = exp(-dt steps sigma) to 1e-5 (65 sums
+    and one product in binary32), 1 for an empty segment, NaN for a broken ray."""
+    import ctypes as C
+    import os
+    _case("gather_twin", n, steps)
+    lib = C.CDLL(os.path.join(os.path.dirname(sf.__file__), "libsf_bench.so"))
+    grid = torch.full((32, 32, 32), 0.75, dtype=torch.float16, device="cuda")
+    vol = sf.Volume(grid, side=1.0, brick_log2=3)
+    rays = np.zeros((n, 8), np.float32)
+    g = np.random.default_rng(n)
+    rays[:, :2] = 0.25 + 0.5 * g.random((n, 2))
+    rays[:, 2] = 0.2
+    rays[:, 5] = 1.0
+    rays[:, 7] = 0.6
+    if n > 2:
+        rays[1, 7] = rays[1, 6]
+        rays[2, 3] = np.nan
+    rd = torch.from_numpy(rays).cuda()
+    T = torch.full((n,), -1.0, device="cuda")
+    p = [C.c_void_p(t.data_ptr()) for t in (grid, vol.occupancy, rd, T)]
+    status = lib.sfb_gather_twin(p[0], 32, 32, 32, (C.c_float * 3)(), (C.c_float * 3)(32, 32, 32), p[1], 3, p[2],
+                                 C.c_int64(n), steps, p[3], C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert status == 0
+    T = T.cpu().numpy()
+    ref = np.full(n, np.exp(-0.75 * 0.6))
+    if n > 2:
+        ref[1], ref[2] = 1.0, np.nan
+    assert np.allclose(T, ref, rtol=1e-5, atol=0, equal_nan=True)
