@@ -167,9 +167,13 @@ def _ptr(t):
 def _stream(stream):
     """The stream's handle, by default the current device's current stream's
     (the handle alone: a ``torch.cuda.Stream`` object round it takes 2.8 us to
-    make, the handle 0.2 us, and a small launch 8 us in all)."""
+    make, the handle 0.2 us, and a small launch 8 us in all; the call for it is
+    private to torch, so the object serves where it is missing)."""
     if stream is None:
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return C.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

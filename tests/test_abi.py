@@ -516,3 +516,14 @@ def test_committed_counters_belong_to_the_timed_kernel(sf):
     spec.loader.exec_module(bench)
     c = bench.counters_from_profile(bench.kernel_code_digest())
     assert c.get("valu_insts_per_launch") and c.get("hbm_bytes_per_launch"), c
+
+
+def test_current_stream_without_torchs_private_call(sf, monkeypatch):
+    """A torch that no longer has the private call for the current stream's
+    handle: the public one gives it."""
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    assert sf._stream(None).value == 0x1234
+    assert sf._stream(types.SimpleNamespace(cuda_stream=0x5678)).value == 0x5678
