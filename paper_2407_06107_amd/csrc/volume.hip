@@ -73,7 +73,7 @@ __device__ __forceinline__ void planck3(float T, float B[3])
         for (int k = 0; k < 3; ++k)
             em1[k] = y[k] < SMALL ? expm1_small(y[k]) : em1[k];
     }
-    const bool cold = T <= 0.0f;
+    const bool cold = T < 0x1p-126f;   // subnormal too: its reciprocal is infinite
 #pragma unroll
     for (int k = 0; k < 3; ++k)
         B[k] = cold ? 0.0f : A[k] * __builtin_amdgcn_rcpf(em1[k]);

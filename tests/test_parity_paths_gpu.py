@@ -609,3 +609,19 @@ def test_non_finite_voxel_reaches_the_rays_that_read_it(sf, cloud48, value, dtyp
             assert np.isnan(b[sure]).all(), mode
         else:
             assert (np.isnan(b[sure]) | (b[sure] <= a[sure])).all() and (b[sure] != a[sure]).any(), mode
+
+
+@pytest.mark.parametrize("T", [1e-45, 1e-40, 1.1754943e-38, 1.17549435e-38, 1.2e-38, 4e-38, 1e-30])
+def test_temperatures_next_to_zero_emit_nothing(sf, T):
+    """Planck's law of a temperature whose reciprocal leaves binary32."""
+    from paper_2407_06107_amd import inputs
+    _case("cold", T)
+    data = np.full((8, 8, 8), T, np.float32)
+    vol = sf.Volume(torch.from_numpy(data).cuda(), side=1.0)
+    rd = torch.from_numpy(inputs.ortho_rays(16, 1, side=1.0, seed=3)).cuda()
+    pos = torch.full((5, 3), 0.5, device="cuda")
+    for filt in (sf.SF_NEAREST, sf.SF_LINEAR, sf.SF_BSPLINE3):
+        for mode in (sf.SF_BEFORE, sf.SF_AFTER_EXACT, sf.SF_STOCHASTIC):
+            smp = sf.sampling(filt, mode)
+            assert (sf.sf_raymarch_emission(vol, rd, 20, smp) == 0).all(), (filt, mode)
+            assert (sf.sf_filter3d(vol, pos, smp, sf.SF_SHADE_PLANCK) == 0).all(), (filt, mode)
