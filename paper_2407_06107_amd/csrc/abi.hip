@@ -826,7 +826,7 @@ static int train_parts(int64_t batch)
 
 // Wavefronts of the matrix-core step: one per pair of 16-sample tiles up to
 // 1024 (one per SIMD of a 256-CU device: each holds the registers of one),
-// then longer chunks.  They leave fewer rows than train_parts(batch), so one
+// then longer chunks.  They leave no more rows than train_parts(batch), so one
 // workspace size serves both modes.
 static int train_waves_mfma(int64_t batch)
 {

@@ -193,9 +193,9 @@ __global__ __launch_bounds__(256) void k_aniso_split(AnisoCall c, int log_g)
     }
 }
 
-// Probe comparators (binary32 weights as the plain deterministic kernel,
-// compensated binary32 sums over up to 64 probes x 2 levels x 16 taps).
-// Deterministic comparators over all taps of all probes.  Bound by the
+// Deterministic comparators over all taps of all probes (binary32 weights as
+// the plain deterministic kernel, compensated binary32 sums over up to
+// 64 probes x 2 levels x 16 taps).  Bound by the
 // arithmetic of the weights and sums and by the wait for the taps; with the
 // texture's format known to the kernel the loads of a level's taps are in flight
 // together.  1279 x 719 pixels of a 4096^2 checkerboard, up to 64 probes: tent

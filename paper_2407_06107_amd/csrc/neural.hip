@@ -1160,7 +1160,8 @@ hipError_t launch_train_reduce(const TrainCall &t, float *workspace, int nparts,
     return hipGetLastError();
 }
 
-// Rows the workspace holds beside the partial ones (part of its size).
+// Rows of the workspace's size beyond the partial ones.  The sum needs none of
+// them any more; the size that callers are asked for stays what it was.
 int train_reduce_chunks(int nparts) { return (nparts + 63) / 64; }
 
 int train_nparams(int C, int O) { return POff(C, O).n; }

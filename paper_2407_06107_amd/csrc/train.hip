@@ -178,7 +178,7 @@ k_train_mfma(TrainCall t, int64_t chunk, float *partials)
     // The weights as fragments (BF16 of the FP32 master parameters): W2
     // forward and backward, W1 forward and W3 backward, W3 forward and W1
     // backward, and the hidden layers' biases; each wavefront's tile, before
-    // the tiles the parameters, and after them two wavefronts' gradients.
+    // the tiles the parameters, and after them a row of gradients per wavefront.
     struct Work {
         uint4 W2[2][8][64], W13[4][64];
         uint2 small[2][4][64];
@@ -196,7 +196,7 @@ k_train_mfma(TrainCall t, int64_t chunk, float *partials)
     const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
 
     // The parameters come in whole lines, then each lane picks its fragments
-    // from LDS: picked from memory, by 2048 wavefronts at once, they took 14 us.
+    // from LDS: picked from memory by each wavefront they took 14 us.
     constexpr int NR = (NP + 64 * TRAIN_WAVES - 1) / (64 * TRAIN_WAVES);   // rounds of the workgroup over them
     {
         float w[NR];
