@@ -252,6 +252,10 @@ struct MarchLanes {
     bool once;
 };
 constexpr MarchLanes STOCH_LANES = {1 << 18, 1 << 17, true};
+// Four lanes and more of a ray read voxels beside each other: twice the lanes
+// apart (4096 rays of 4 samples in the 256^3 fire, nearest, 14.5 us; 18.1 within
+// 2^17 lanes).
+constexpr MarchLanes SHARED_LANES = {1 << 18, 1 << 18, true};
 struct SplitGrid {
     uint32_t blocks, lanes;
     SplitArgs args;

@@ -800,7 +800,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
     int st = 3;   // no ray (the whole group of lanes shares i)
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    rg.share(sp, rays_together(g, st == 0, c.steps), c.steps);
+    rg.share(sp, rays_together(g, st == 0, c.steps, lane == 0), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     __amdgpu_buffer_rsrc_t rm;
@@ -1283,7 +1283,7 @@ template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
 static void launch_emit_stoch(const RaymarchCall &c, hipStream_t s)
 {
     const int G = lane_group(c.n, c.spp);
-    const SplitGrid sg(c.n * G, c.steps, 4, STOCH_LANES);
+    const SplitGrid sg(c.n * G, c.steps, 4, G > 2 ? SHARED_LANES : STOCH_LANES);
     const int lg = __builtin_ctz(G);
     if (c.footprint > 0.0f)
         k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args, lg);

@@ -166,13 +166,16 @@ struct RaySplit {
 
 // Whether the wavefront's rays lie together: of the lanes that march beside
 // one that does, three in four are within 16 voxels of it half-way.  All lanes
-// call it; the wavefronts of the same rays find the same.
-__device__ __forceinline__ bool rays_together(const RayGeom &g, bool march, int steps)
+// call it; the wavefronts of the same rays find the same.  Where adjacent lanes
+// have one ray only the `first` of each counts; sixteen and more (no row of 16
+// holds two rays) share lines enough to be together.
+__device__ __forceinline__ bool rays_together(const RayGeom &g, bool march, int steps, bool first = true)
 {
     float p[3];
     int i0[3];
     step_pos(g, 0.5f * (float)steps, p, i0);
-    const bool pair = march & (__builtin_amdgcn_update_dpp(0, (int)march, 0x111, 0xf, 0xf, false) != 0);   // row_shr:1
+    const bool pair =
+        march & first & (__builtin_amdgcn_update_dpp(0, (int)march, 0x111, 0xf, 0xf, false) != 0);   // row_shr:1
     bool near = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a)

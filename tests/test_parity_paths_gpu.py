@@ -625,3 +625,28 @@ def test_temperatures_next_to_zero_emit_nothing(sf, T):
             smp = sf.sampling(filt, mode)
             assert (sf.sf_raymarch_emission(vol, rd, 20, smp) == 0).all(), (filt, mode)
             assert (sf.sf_filter3d(vol, pos, smp, sf.SF_SHADE_PLANCK) == 0).all(), (filt, mode)
+
+
+# two, four and eight adjacent lanes per ray, sixteen and more (a row of lanes
+# holds no second ray), rays together and apart, few and many of them
+@pytest.mark.parametrize("apart", [False, True])
+@pytest.mark.parametrize("n, spp", [(300, 4), (9000, 4), (33000, 4), (3000, 2), (3000, 8), (3000, 16), (500, 64)])
+def test_emission_lanes_of_a_ray_share_its_steps(sf, orc, cloud48, apart, n, spp):
+    """Stochastic emission against the oracle to 1e-5, with and without the
+    brick mask."""
+    from paper_2407_06107_amd import inputs
+    _case("emission_lanes", apart, n, spp)
+    data = cloud48[:40, :36, :44].astype(np.float32)
+    hot = np.where(data > 0, 800 + 5200 * np.sqrt(data / data.max()), 0).astype(np.float16)
+    near = inputs.ortho_rays(192, 1, side=1.0, seed=3)
+    first = (len(near) - n) // 2   # (the first rays miss)
+    rays = inputs.random_rays(n, 1.0, seed=8) if apart else near[first:first + n]
+    rd = torch.from_numpy(np.ascontiguousarray(rays.astype(np.float32))).cuda()
+    og, vol = _grids(orc, sf, hot)
+    _, volm = _grids(orc, sf, hot, brick=2)
+    smp = sf.sampling(sf.SF_BSPLINE3, sf.SF_STOCHASTIC, spp, seed=5)
+    ref = orc.raymarch_emission(og, rays, 40, orc.BSPLINE3, orc.STOCHASTIC, spp=spp, seed=5)
+    top = ref.max(axis=0)
+    for v in (vol, volm):
+        L = sf.sf_raymarch_emission(v, rd, 40, smp).cpu().numpy()
+        assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6)
