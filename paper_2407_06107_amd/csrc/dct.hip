@@ -135,7 +135,10 @@ __device__ __forceinline__ void block_coeffs(const uint8_t *lv, int wl, int hl, 
 // level, kept until the second pass in the 16 bytes of the first of those
 // blocks (which no code has been written to yet).  An atomic maximum per
 // wavefront and channel on dst_range instead queued 22,000 atomics of a
-// 4096^2 pyramid on one line: 190 of the pass's 267 us.
+// 4096^2 pyramid on one line: 190 of the pass's 267 us.  The maxima of a
+// launch's only workgroup (256 blocks) are the levels' already, and go to
+// c.range without the pass between (64^2 and its levels, a call: 26.4 us with
+// it, 22.6 without).
 __global__ __launch_bounds__(256) void k_dct_range(DctEncodeCall c)
 {
     __shared__ float part[4][4];
@@ -172,8 +175,10 @@ __global__ __launch_bounds__(256) void k_dct_range(DctEncodeCall c)
         if (threadIdx.x < 4) {
             const int ch = threadIdx.x;
             const int64_t j = max(b0, c.first_block[lv]) - c.first_block[lv];
-            reinterpret_cast<float *>(c.dst + c.dst_off[lv])[4 * j + ch] = __builtin_fmaxf(
-                __builtin_fmaxf(part[0][ch], part[1][ch]), __builtin_fmaxf(part[2][ch], part[3][ch]));
+            float *to = gridDim.x == 1 ? c.range + 4 * lv
+                                       : reinterpret_cast<float *>(c.dst + c.dst_off[lv]) + 4 * j;
+            to[ch] = __builtin_fmaxf(__builtin_fmaxf(part[0][ch], part[1][ch]),
+                                     __builtin_fmaxf(part[2][ch], part[3][ch]));
         }
         __syncthreads();
     }
@@ -251,7 +256,8 @@ hipError_t launch_dct_encode(const DctEncodeCall &c, hipStream_t s)
     const int64_t nb = c.first_block[c.levels];
     const dim3 grid((uint32_t)((nb + 255) / 256)), block(256);
     k_dct_range<<<grid, block, 0, s>>>(c);
-    k_dct_range_level<<<dim3((uint32_t)c.levels), dim3(1024), 0, s>>>(c);
+    if (grid.x > 1)
+        k_dct_range_level<<<dim3((uint32_t)c.levels), dim3(1024), 0, s>>>(c);
     k_dct_codes<<<grid, block, 0, s>>>(c);
     return hipGetLastError();
 }

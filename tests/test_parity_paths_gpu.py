@@ -650,3 +650,21 @@ def test_emission_lanes_of_a_ray_share_its_steps(sf, orc, cloud48, apart, n, spp
     for v in (vol, volm):
         L = sf.sf_raymarch_emission(v, rd, 40, smp).cpu().numpy()
         assert np.allclose(L / top, ref / top, rtol=1e-5, atol=1e-6)
+
+
+# one workgroup of 256 blocks in all, one block more, and a pyramid of each
+@pytest.mark.parametrize("w, h, levels", [(128, 128, 1), (121, 127, 1), (8, 2056, 1), (128, 129, 1), (104, 112, 7), (112, 120, 7),
+                                          (64, 64, 7), (1, 1, 1)])
+def test_dct_codes_of_one_workgroup(sf, orc, w, h, levels):
+    """Codes and AC ranges equal the oracle's bit for bit where the first
+    pass's maxima are the levels' ranges themselves, and where not."""
+    _case("dct_one_workgroup", w, h, levels)
+    lv = _pyramid(w, h, 100 * w + h)[:levels]
+    ot = orc.Tex2D.dct(lv)
+    gt = sf.Texture2D.dct(sf.Texture2D(lv))
+    torch.cuda.synchronize()
+    buf = gt.buffer.cpu().numpy()
+    for l, x in enumerate(lv):
+        n = 16 * (-(-x.shape[1] // 8)) * (-(-x.shape[0] // 8))
+        assert np.array_equal(buf[gt.offsets[l]:gt.offsets[l] + n], ot.buf[ot.off[l]:ot.off[l] + n]), l
+    assert np.array_equal(gt.ranges.cpu().numpy(), ot.dct_range)
