@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_ray_stoch(RaymarchCall
     int st = 3;   // no ray
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    r.share(sp, rays_together(g, st == 0, c.steps), c.steps);
+    r.share(sp, sp.log_apart == sp.log_split || rays_together(g, st == 0, c.steps), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     // optical depth and the mean over samples as compensated binary32 sums:
@@ -800,7 +800,7 @@ __global__ __launch_bounds__(64 * MAX_SPLIT_WAVES) void k_emit_stoch(RaymarchCal
     int st = 3;   // no ray (the whole group of lanes shares i)
     if (i < c.n)
         st = ray_setup_dev(c.vol.wmin, c.vol.scale, c.rays + 8 * i, c.steps, g);
-    rg.share(sp, rays_together(g, st == 0, c.steps, lane == 0), c.steps);
+    rg.share(sp, sp.log_apart == sp.log_split || rays_together(g, st == 0, c.steps, lane == 0), c.steps);
     __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(c.vol.base), 0,
                                                                   (int)c.vol.bytes, kBufferFlags);
     __amdgpu_buffer_rsrc_t rm;

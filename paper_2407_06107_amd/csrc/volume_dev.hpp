@@ -165,7 +165,8 @@ struct RaySplit {
 };
 
 // Whether the wavefront's rays lie together: of the lanes that march beside
-// one that does, three in four are within 16 voxels of it half-way.  All lanes
+// one that does, three in four are within 16 voxels of it half-way.  Asked only
+// where the answer makes a difference (3% of a march of 44 steps).  All lanes
 // call it; the wavefronts of the same rays find the same.  Where adjacent lanes
 // have one ray only the `first` of each counts; sixteen and more (no row of 16
 // holds two rays) share lines enough to be together.
