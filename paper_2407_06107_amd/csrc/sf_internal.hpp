@@ -238,24 +238,29 @@ constexpr int MAX_SPLIT_WAVES = 16;
 // Launch shape of a march of n rays: workgroups of `lanes` lanes, each ray
 // over 2^log_split wavefronts, until there are `wanted` lanes, 2^most
 // wavefronts per ray or fewer than 16 steps each.  Stochastic marches (`once`)
-// read one voxel a step and want 2^18 lanes, half of what the chip holds, and
+// read one voxel a step and want 2^19 lanes, what the chip holds, and
 // one split up to 2 Mi rays; marches over every tap want more, the more taps (a
 // staged box is a long wait).  Rays that lie apart (rays_together) are split
-// only up to `apart` lanes, while all wavefronts launched fit the chip at once
+// only up to `apart` lanes, while all wavefronts launched `fit` the chip at once
 // (past that, those without steps would keep others out).  256 steps, 256^3
-// binary16 cloud, trilinear, us with a quarter of `wanted`, with it and with
-// four times it: stochastic, 64 x 64 pixels of 16 rays 53, 38 and 40, 65,536 random
-// rays 159, 160 and 186; exact after, 128 x 128 pixels of 16 501, 298 and 298.
-// 65,536 random rays without the limit of `apart`: exact after 615, 554 with it.
+// binary16 cloud and fire, us within 2^18 lanes and 2^19: 100 x 100 pixels of
+// 16 rays, tricubic stochastic 111 and 99, emission 160 and 145, with a
+// footprint 285 and 255; 65,536 random rays 171 and 173, 173 and 177, 193 and
+// 225; trilinear stochastic within 2^16 and 2^20, 64 x 64 pixels of 16 53 and 40, random
+// 159 and 186.  Exact after trilinear, 128 x 128 pixels of 16, with a quarter of its
+// 2^20, with them and with four times as many: 501, 298 and 298; 65,536 random rays
+// without the limit of `apart` 615, with it 554.
 struct MarchLanes {
-    int64_t wanted, apart;
+    int64_t wanted, apart, fit;
     bool once;
 };
-constexpr MarchLanes STOCH_LANES = {1 << 18, 1 << 17, true};
+constexpr MarchLanes STOCH_LANES = {1 << 19, 1 << 17, 1 << 19, true};
+// A march with a footprint has registers for seven wavefronts per SIMD, not eight.
+constexpr MarchLanes FOOTPRINT_LANES = {1 << 19, 1 << 17, 1 << 18, true};
 // Four lanes and more of a ray read voxels beside each other: twice the lanes
 // apart (4096 rays of 4 samples in the 256^3 fire, nearest, 14.5 us; 18.1 within
 // 2^17 lanes).
-constexpr MarchLanes SHARED_LANES = {1 << 18, 1 << 18, true};
+constexpr MarchLanes SHARED_LANES = {1 << 18, 1 << 18, 1 << 19, true};
 struct SplitGrid {
     uint32_t blocks, lanes;
     SplitArgs args;
@@ -267,7 +272,7 @@ struct SplitGrid {
             ++log_split;
         while (log_apart < log_split && (n << (log_apart + 1)) <= m.apart)
             ++log_apart;
-        if ((n << log_split) > (1 << 19))
+        if ((n << log_split) > m.fit)
             log_apart = log_split;
         lanes = 64u << (log_split > 2 ? log_split : 2);
         const uint32_t rays = lanes >> log_split;

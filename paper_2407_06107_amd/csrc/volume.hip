@@ -1232,9 +1232,9 @@ hipError_t launch_build_occupancy(const VolArgs &v, uint32_t *occ, hipStream_t s
 static uint32_t blocks_for(int64_t n) { return (uint32_t)((n + 255) / 256); }
 
 template <int F>
-constexpr MarchLanes DET_LANES = F == NEAREST   ? MarchLanes{1 << 19, 1 << 17, false}
-                                 : F == LINEAR ? MarchLanes{1 << 20, 1 << 16, false}
-                                               : MarchLanes{1 << 21, 1 << 18, false};
+constexpr MarchLanes DET_LANES = F == NEAREST   ? MarchLanes{1 << 19, 1 << 17, 1 << 19, false}
+                                 : F == LINEAR ? MarchLanes{1 << 20, 1 << 16, 1 << 19, false}
+                                               : MarchLanes{1 << 21, 1 << 18, 1 << 19, false};
 
 template <int F, bool HALF, bool OCC, bool P2>
 static void launch_ray_fo(const RaymarchCall &c, hipStream_t s)
@@ -1283,7 +1283,8 @@ template <int F, bool HALF, int VAR, bool DBG, bool OCC, bool P2>
 static void launch_emit_stoch(const RaymarchCall &c, hipStream_t s)
 {
     const int G = lane_group(c.n, c.spp);
-    const SplitGrid sg(c.n * G, c.steps, 4, G > 2 ? SHARED_LANES : STOCH_LANES);
+    const SplitGrid sg(c.n * G, c.steps, 4,
+                       G > 2 ? SHARED_LANES : (c.footprint > 0.0f ? FOOTPRINT_LANES : STOCH_LANES));
     const int lg = __builtin_ctz(G);
     if (c.footprint > 0.0f)
         k_emit_stoch<F, HALF, VAR, DBG, OCC, P2, true><<<dim3(sg.blocks), dim3(sg.lanes), 0, s>>>(c, sg.args, lg);
