@@ -139,8 +139,8 @@ __device__ __forceinline__ void step_coords(const RayGeom &g, float kh, int i0[3
 // caches.  Rays that lie apart share no lines, and more of them on their way at
 // once find fewer: those are split over 2^log_apart wavefronts only, and the
 // group's others have no steps.  65,536 rays x 256 steps, trilinear stochastic, 256^3
-// binary16 cloud: 64 x 64 pixels of 16 rays 97 us unsplit, 57 in 16 stretches and 38
-// in turns of four; random rays 159, 242 and 160 us.
+// binary16 cloud: 64 x 64 pixels of 16 rays 97 us unsplit, 57 in 16 stretches and 40
+// in turns of eight; random rays 159, 242 and 163 us (two take steps).
 struct RaySplit {
     int64_t i;         // ray
     int wave, lane;
